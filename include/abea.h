@@ -453,7 +453,7 @@ typedef struct {
   int32_t cells_per_lane;
   int32_t waves_per_group;
   uint64_t trace_bytes;    /* device trace memory of the batch */
-  uint64_t scratch_bytes;  /* device pair scratch of the batch */
+  uint64_t scratch_bytes;  /* device path scratch of the batch */
   int32_t band_clear;      /* ABEA_CLEAR_WINDOW or ABEA_CLEAR_EDGES, as resolved */
   int32_t parts;           /* split kernels: parts the batch runs in under the trace budget;
                               fused kernel: 1 */

@@ -198,7 +198,8 @@ bool edge_clearing(const abea_ctx *ctx, int waves) {
  *  - Reads are sorted by computed bands (n_e + n_k - 1, 0 for an empty read),
  *    longest first, so the longest band chains start first and every read
  *    fits the trace region of any read planned before it.
- *  - Pair scratch: n_e + n_k - 1 slots per read (a path never has more).
+ *  - Path scratch: two bits per computed band, and a word pair per segment of
+ *    the walk (path_words).
  *  - Trace, fused kernel with P workers: read s < P gets its own region and
  *    worker s reuses it for every later read it takes; P is the requested
  *    worker count, capped by residency and by the trace budget (admission by
@@ -304,7 +305,7 @@ int plan_batch(abea_ctx *ctx, Work &w, int n, const uint64_t *eo, const uint64_t
     transitions((int64_t)ne, (int64_t)nk, &d.lp_skip, &d.lp_stay, &d.lp_step);
     if (s < workers) tr += words(s);
     tr_max = std::max(tr_max, tr);
-    pr += comp[r];
+    pr += path_words(comp[r], ctx->cpl);
   }
   P.parts.push_back(n);
   P.n_trace = tr_max;
@@ -420,8 +421,8 @@ int enqueue_kernels(abea_ctx *ctx, Work &w, const DevIO &io, hipStream_t st, boo
   if (timed) HIP_TRY(ctx, hipEventRecord(w.tev[4], st));
 
   HIP_TRY(ctx, launch_scan((const uint64_t *)w.path_len.p, n, io.pair_offset, st));
-  HIP_TRY(ctx, launch_compact((const int2 *)w.scratch.p, (const uint64_t *)w.path_src.p,
-                              io.pair_offset, n, io.pairs, st));
+  HIP_TRY(ctx, launch_expand(reads, n, P.cpl, (const int2 *)w.scratch.p, (const uint64_t *)w.path_src.p,
+                             io.pair_offset, io.pairs, st));
   if (timed) HIP_TRY(ctx, hipEventRecord(w.tev[5], st));
   w.timed = timed;
   return ABEA_OK;

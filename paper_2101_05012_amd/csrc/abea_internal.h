@@ -17,7 +17,7 @@ struct ReadDesc {
   uint64_t km_off;  /* first k-mer of the read */
   uint64_t tr_off;  /* first trace tile word (uint2 units) */
   uint64_t spare;
-  uint64_t pr_off;  /* first slot of the read's pair scratch (n_e+n_k-1 slots) */
+  uint64_t pr_off;  /* first word pair of the read's path scratch (path_words) */
   int32_t n_e;
   int32_t n_k;
   float lp_skip;
@@ -63,8 +63,31 @@ inline int cells_per_lane(int W) {
   return c;
 }
 
-/* Trace-tile groups held in a wavefront's LDS ring during the backtrack. */
-constexpr int BT_RING_GROUPS = 16;
+/* The walk's segments (see backtrack_read): a path of ng trace groups is cut
+ * into segments of sl groups; returns their number.  Four groups or more a
+ * segment: a lane also walks the overlap above its own, so smaller ones save
+ * nothing. */
+constexpr int WALK_MAX_SEGMENTS = 64; /* lanes of the walking wavefront */
+constexpr int WALK_MIN_GROUPS = 4;
+/* bands a segment's walk starts above its segment.  64 reads of 1 kb take 367 /
+ * 365 / 372 / 378 us and 100 reads of up to 1 Mb 308 / 303 / 303 / 304 ms at 96 /
+ * 128 / 192 / 256: at 96 some segments walk again */
+constexpr int WALK_OVERLAP = 128;
+__host__ __device__ inline int path_segments(int ng, int &sl) {
+  int n = ng / WALK_MIN_GROUPS;
+  n = n < 1 ? 1 : n > WALK_MAX_SEGMENTS ? WALK_MAX_SEGMENTS : n;
+  sl = (ng + n - 1) / n;
+  return (ng + sl - 1) / sl;
+}
+/* Word pairs of the path scratch of a read of `bands` computed bands: one per
+ * trace group, and one per segment where the path can have more than one (a
+ * shorter path, with trim states, has no more of either).  Never more than
+ * one per band. */
+inline uint64_t path_words(uint64_t bands, int cpl) {
+  const uint64_t groups = (bands + bands_per_group(cpl) - 1) / bands_per_group(cpl);
+  const uint64_t n = groups / WALK_MIN_GROUPS;
+  return groups + (n > 1 ? (n < WALK_MAX_SEGMENTS ? n : WALK_MAX_SEGMENTS) : 0);
+}
 
 /* Arguments of the band, backtrack and fused alignment kernels. */
 struct AlignArgs {
@@ -85,9 +108,9 @@ struct AlignArgs {
   const float *shift;    /* [caller reads] */
   int32_t *rstat;        /* [n_reads] status from k_prep; k_band writes the band outcome */
   uint2 *trace;          /* bit-plane trace tiles: 64 lanes x uint2 per group of bands */
-  int2 *scratch;         /* reversed-path pair scratch */
+  int2 *scratch;         /* path scratch: the paths as bits (see backtrack_read) */
   uint64_t *path_len;    /* [caller reads] by original index */
-  uint64_t *path_src;    /* [caller reads] by original index: first scratch slot of the path */
+  uint64_t *path_src;    /* [caller reads] by original index: trace groups the path covers */
   float *out_ll;         /* [caller reads] by original index */
   uint64_t *out_cells;   /* [caller reads] by original index, or null */
   int32_t *out_status;   /* [caller reads] by original index */
@@ -138,8 +161,9 @@ constexpr int NOALLOC_MAX_DEVICES = 64;
 /* The device address of `device`'s scratch array (hipGetSymbolAddress on
  * the first call for that device, which must be the current device). */
 hipError_t noalloc_scratch(int device, void **ptr);
-hipError_t launch_compact(const int2 *scratch, const uint64_t *path_src, const uint64_t *offset,
-                          int n, int2 *pairs, hipStream_t st);
+/* the pairs of n planned reads from their path bits */
+hipError_t launch_expand(const ReadDesc *reads, int n, int cpl, const int2 *scratch, const uint64_t *path_src,
+                         const uint64_t *offset, int2 *pairs, hipStream_t st);
 
 /* ---- event detection (abea_detect.hip) ---- */
 constexpr int ED_TILE = 1024;       /* boundaries per tile of one read */

@@ -30,16 +30,17 @@
  *              bands of launches that fill the SIMDs) only the two beside the
  *              band.  Only two trace bits per slot reach HBM (two bit planes,
  *              32/CPL bands per 32-bit word).
- *  k_backtrack one wavefront per read walks the path with wave-uniform scalar
- *              state: the trace bits of cell (e, k) are in group (e+k)/G, lane
- *              (k mod N)/CPL, so no band positions are needed.  Trace tiles
- *              stream through an LDS ring; pairs are gathered in lanes, up to
- *              64 at a time, and stored coalesced.
+ *  k_backtrack one wavefront per read walks the path, its trace cut into up to
+ *              64 segments walked at once, one lane each, from guessed starts
+ *              that are checked against the segment above and walked again
+ *              where they differ.  The trace bits of cell (e, k) are in group
+ *              (e+k)/G, lane (k mod N)/CPL.  The path is kept as two bits per
+ *              band.
  *  k_align     the fused form: each wavefront fills a read's bands and then
  *              walks it, one read per wavefront or a persistent pool taking
  *              reads from a device work queue.
- *  k_scan/k_compact turn per-read path lengths into the caller's compact
- *              pair layout.
+ *  k_scan/k_expand turn per-read path lengths into the caller's pair offsets
+ *              and the path bits into its pairs.
  *
  * Arithmetic of a cell follows Alg. 5.2 and 5.3 exactly as the CPU reference
  * does: FP32, no contraction (-ffp-contract=off and the pragma below), the
@@ -50,6 +51,7 @@
 
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -58,6 +60,8 @@
 namespace abea {
 
 #define ABEA_NINF (-__builtin_inff())
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 template <int CPL>
 struct Log2 {
@@ -188,6 +192,31 @@ __global__ __launch_bounds__(256) void k_prep(const ReadDesc *__restrict__ reads
   } else {
     for (int e = threadIdx.x; e < rd.n_e; e += blockDim.x) xmean[rd.ev_off + e] = ev[(int64_t)ev_stride * e];
   }
+}
+
+/* The arguments of the alignment kernels (their only parameter), read again
+ * from the kernel argument segment, and the lane index made again: the
+ * compiler may keep neither, nor what it derives from them, in registers
+ * across this point, so the band fill and the walk of a fused kernel each hold
+ * only what they use. */
+typedef const __attribute__((address_space(4))) AlignArgs KernArgs;
+__device__ __forceinline__ KernArgs &kernel_args() {
+  KernArgs *p = (KernArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *p;
+}
+/* planned read s (the plan does not change while a kernel runs: scalar loads) */
+__device__ __forceinline__ ReadDesc read_desc(const ReadDesc *reads, int s) {
+  const __attribute__((address_space(4))) ReadDesc *p =
+      (const __attribute__((address_space(4))) ReadDesc *)(uint64_t)(reads + s);
+  ReadDesc d;
+  __builtin_memcpy(&d, (const void *)p, sizeof d);
+  return d;
+}
+__device__ __forceinline__ int fresh_lane() {
+  int l = threadIdx.x & 63;
+  asm volatile("" : "+v"(l));
+  return l;
 }
 
 /* ------------------------------------------------------------------ band */
@@ -358,10 +387,19 @@ struct Geom {
   static constexpr int XS = RX / S + G / S;
 };
 
+/* 16-byte pieces of a trace group (two lanes' words) that the walk keeps per
+ * segment: the walk enters a group at a k-mer no higher than where it entered
+ * the group above, when the pieces were requested, and falls 2-3 k-mers per 8
+ * bands; a step outside them reads memory. */
+template <int CPL>
+struct WalkGeom {
+  static constexpr int NP = CPL == 1 ? 8 : CPL == 2 ? 6 : CPL == 4 ? 3 : 2;
+};
+
 /* LDS of one wavefront: the band fill's event ring (S sub-rings, each with a
  * mirror of its first G/S entries behind its end, so that a run of G reads
- * never wraps) and k-mer ring, or the backtrack's trace-tile ring; the two
- * phases of a read never overlap. */
+ * never wraps) and k-mer ring, or the walk's pieces of trace groups, one row
+ * of 64 segments per piece; the two phases of a read never overlap. */
 template <int CPL>
 struct WaveLds {
   union {
@@ -369,7 +407,7 @@ struct WaveLds {
       float lx[Geom<CPL>::S * Geom<CPL>::XS];
       float4 lk[Geom<CPL>::RK];
     } band;
-    uint2 ring[BT_RING_GROUPS * 64];
+    u32x4 win[WalkGeom<CPL>::NP * 64];
   };
 };
 
@@ -398,7 +436,7 @@ struct WaveLds {
  * stale ring entries) never reaches the band, its end cells or the trace bits
  * of its cells. */
 template <int CPL, int RPG, int CLEAR, bool TRIM>
-__device__ __forceinline__ int band_read(const AlignArgs &a, const ReadDesc &rd, uint2 *trace,
+__device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 *trace,
                                          float *__restrict__ lx, float4 *__restrict__ lk, int &e_end) {
   /* CLEAR: slot clearing of interior bands, 0 the window, 1 the two edge
    * slots, 2 the two edge slots with W even at two slots per lane (then the
@@ -420,7 +458,7 @@ __device__ __forceinline__ int band_read(const AlignArgs &a, const ReadDesc &rd,
   constexpr int RF = G / RPG; /* bands between slot refills (RPG refills per group) */
   static_assert(RF >= 2 && RF % 2 == 0, "refill interval must be an even band count");
 
-  const int lane = threadIdx.x & 63;
+  const int lane = fresh_lane();
   const int n_e = rd.n_e, n_k = rd.n_k;
   const int W = a.W;
 
@@ -788,9 +826,19 @@ __device__ __forceinline__ int band_read(const AlignArgs &a, const ReadDesc &rd,
    * interior test once per group, one trace word per lane per group. */
   int i = 2;
   uint64_t g = 0;
+  /* K at the start of each group, for the walk (64 groups gathered in lanes,
+   * then one coalesced store), in the read's path scratch, which the walk
+   * fills only after it has read them */
+  int kgat = 0;
+  int *__restrict__ kpos = reinterpret_cast<int *>(a.scratch + rd.pr_off);
+  auto note_k = [&]() {
+    kgat = writelane(K, (int)g & 63, kgat);
+    if (((int)g & 63) == 63) kpos[(g & ~63ull) + lane] = kgat;
+  };
   const bool gap_ok = N - W >= CPL; /* interior bands clear CPL slots outside the band */
   while (i + G - 1 <= last) {
     K = __builtin_amdgcn_readfirstlane(K);
+    note_k();
     E = i - 3 - K; /* band i - 1 is the latest */
     advance_rings();
     /* with trim the last k-mer stays out of interior bands, whose cells the
@@ -810,6 +858,7 @@ __device__ __forceinline__ int band_read(const AlignArgs &a, const ReadDesc &rd,
   /* the last, partial group */
   if (i <= last) {
     K = __builtin_amdgcn_readfirstlane(K);
+    note_k();
     E = i - 3 - K;
     advance_rings();
     const int gb = last - i + 1;
@@ -828,7 +877,9 @@ __device__ __forceinline__ int band_read(const AlignArgs &a, const ReadDesc &rd,
     i = last + 1;
     const int sh = (G - gb) * CPL;
     trace[g * 64 + lane] = make_uint2(TD << sh, TU << sh);
+    ++g;
   }
+  if (lane < ((int)g & 63)) kpos[(g & ~63ull) + lane] = kgat;
 
   /* terminal cell (n_e-1, n_k-1) is in the last band if its k-mer is; with
    * trim the end cell the end recurrence chose */
@@ -860,7 +911,7 @@ __device__ __forceinline__ int band_read(const AlignArgs &a, const ReadDesc &rd,
 }
 
 /* Outputs of a read whose band fill did not run (an empty read). */
-__device__ __forceinline__ void band_skipped(const AlignArgs &a, const ReadDesc &rd) {
+__device__ __forceinline__ void band_skipped(KernArgs &a, const ReadDesc &rd) {
   if ((threadIdx.x & 63) == 0) {
     a.out_ll[rd.orig] = ABEA_NINF;
     if (a.out_cells) a.out_cells[rd.orig] = 0;
@@ -874,14 +925,14 @@ __global__ __launch_bounds__(64) void k_band(const AlignArgs a) {
   const int s = blockIdx.x;
   const ReadDesc rd = a.reads[s];
   if (a.rstat[s] != READ_OK) {
-    band_skipped(a, rd);
+    band_skipped(kernel_args(), rd);
     return;
   }
   /* the longest reads set the kernel's duration: let them issue first */
   const bool urgent = rd.n_e + rd.n_k >= a.urgent_len;
   if (urgent) __builtin_amdgcn_s_setprio(2);
   int e_end;
-  const int st = band_read<CPL, RPG, EDGE, TRIM>(a, rd, a.trace + rd.tr_off, lds.band.lx, lds.band.lk, e_end);
+  const int st = band_read<CPL, RPG, EDGE, TRIM>(kernel_args(), rd, a.trace + rd.tr_off, lds.band.lx, lds.band.lk, e_end);
   if (urgent) __builtin_amdgcn_s_setprio(0);
   if (threadIdx.x == 0) {
     a.rstat[s] = st;
@@ -891,66 +942,64 @@ __global__ __launch_bounds__(64) void k_band(const AlignArgs a) {
 
 /* ------------------------------------------------------------- backtrack */
 
-/* Bit of trace cell (band t, slot k) in its lane's 32-bit word: 31 - ((t mod
- * G) * CPL + k mod CPL), as (~((t << LC) + (k & (CPL - 1)))) & 31 in three
- * SALU instructions (the compiler would rebuild the five-instruction form). */
-template <int CPL>
-__device__ __forceinline__ int trace_bit(int t, int k) {
-  int b;
-  if constexpr (CPL == 1) {
-    asm("s_andn2_b32 %0, 31, %1" : "=s"(b) : "s"(t));
-  } else {
-    int m;
-    if constexpr (CPL == 2)
-      asm("s_and_b32 %1, %3, 1\n\ts_lshl1_add_u32 %0, %2, %1\n\ts_andn2_b32 %0, 31, %0"
-          : "=&s"(b), "=&s"(m) : "s"(t), "s"(k) : "scc");
-    else if constexpr (CPL == 4)
-      asm("s_and_b32 %1, %3, 3\n\ts_lshl2_add_u32 %0, %2, %1\n\ts_andn2_b32 %0, 31, %0"
-          : "=&s"(b), "=&s"(m) : "s"(t), "s"(k) : "scc");
-    else if constexpr (CPL == 8)
-      asm("s_and_b32 %1, %3, 7\n\ts_lshl3_add_u32 %0, %2, %1\n\ts_andn2_b32 %0, 31, %0"
-          : "=&s"(b), "=&s"(m) : "s"(t), "s"(k) : "scc");
-    else
-      asm("s_and_b32 %1, %3, 15\n\ts_lshl4_add_u32 %0, %2, %1\n\ts_andn2_b32 %0, 31, %0"
-          : "=&s"(b), "=&s"(m) : "s"(t), "s"(k) : "scc");
-  }
-  return b;
-}
+/* value of lane l+1 in lane l (the last lane keeps its own) */
+__device__ __forceinline__ int from_above(int v) { return __shfl_down(v, 1, 64); }
 
-/* The walk's move from its cell (t = e + k, k), whose trace bits sit at bit
- * `bit` of the lane's words: t falls by 1, and by 2 on a diagonal (D bit);
- * k falls unless the move is up (D bit, or no U bit: the word wk = D | ~U).
- * Each bit goes straight into SCC (s_bitcmp1) and one subtract with borrow
- * applies it: four SALU instructions. */
-__device__ __forceinline__ void walk_move(int &t, int &k, uint32_t wd, uint32_t wk, int bit) {
-  asm("s_bitcmp1_b32 %2, %4\n\t"
-      "s_subb_u32 %0, %0, 1\n\t"
-      "s_bitcmp1_b32 %3, %4\n\t"
-      "s_subb_u32 %1, %1, 0"
-      : "+s"(t), "+s"(k)
-      : "s"(wd), "s"(wk), "s"(bit)
-      : "scc");
+/* Inclusive sum over the lanes of a wavefront. */
+__device__ __forceinline__ uint32_t lane_scan(uint32_t v) {
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t o = __shfl_up(v, d, 64);
+    if ((int)(threadIdx.x & 63) >= d) v += o;
+  }
+  return v;
 }
 
 /* Backtrack of one read (Alg. 5.1, after the band loop) by the calling
- * wavefront, from its trace tiles: writes the path's pairs backwards into
- * the read's scratch slots, its length and first slot, and its final status
- * (and -inf as log-likelihood if the walk fails).  The walk starts at
- * (e_start, n_k-1): (n_e-1, n_k-1), or with TRIM the end cell the band fill
- * chose; it ends at the origin, or with TRIM on reaching the trim column
- * k = -1 (whose cells are not pairs). */
+ * wavefront, from its trace tiles: writes the path as bits (path scratch), its
+ * length, the trace groups it covers and the read's final status (and -inf as
+ * log-likelihood if the walk fails).  The walk starts at (e_start, n_k-1):
+ * (n_e-1, n_k-1), or with TRIM the end cell the band fill chose; it ends at the
+ * origin, or with TRIM on reaching the trim column k = -1 (whose cells are not
+ * pairs).
+ *
+ * What bounds it: a step needs the trace word of its cell, and the next cell
+ * depends on it, so one walk is a chain of load, decode, move (60 ns a cell
+ * as a wave-uniform scalar walk, a quarter of a long read's time).  Here the
+ * trace groups are cut into up to 64 segments, one lane each, walked at once.
+ * Where a segment's walk starts is known only when the segment above is done,
+ * so each lane starts WALK_OVERLAP bands higher, from the middle of the band
+ * there (the K the band fill noted): the best paths to the cells of a band come
+ * from one cell a few dozen bands below, so by the segment's top the guess has
+ * met the path.  That is checked, not assumed: a lane whose walk entered its
+ * segment elsewhere than the segment above left it walks again from there,
+ * until every lane agrees with the one above, the topmost being exact from the
+ * start.  The path is then the one cell-by-cell walk's, whatever the guesses.
+ *
+ * All lanes take a group at a time.  A step handles a run of up moves at once:
+ * the run ends at the first cell of the column whose move lowers k (D bit, or
+ * no U bit: wk = D | ~U), found by one find-first-bit over the column's bits of
+ * the word.  The words a lane needs next lie in a few 16-byte pieces of the
+ * group below, requested while the current group is walked (WalkGeom) and kept
+ * in LDS.
+ *
+ * Path scratch of a read: one word pair (V, M) per group, bit b for the cell of
+ * band g*G + b: V set if the path visits the band, M if k falls on leaving that
+ * cell; then, with more than one segment, the count of path cells and of M bits
+ * below each segment. */
 template <int CPL, bool TRIM>
-__device__ __forceinline__ void backtrack_read(const AlignArgs &a, const ReadDesc &rd, int status, int e_start,
-                                               const uint2 *__restrict__ tr,
-                                               uint2 *__restrict__ ring) {
+__device__ __forceinline__ void backtrack_read(KernArgs &a, const ReadDesc &rd, int status, int e_start,
+                                               const uint2 *tr, u32x4 *win) {
   constexpr int N = 64 * CPL;
   constexpr int LC = Log2<CPL>::v;
   constexpr int LG = 5 - LC;           /* log2(G) */
   constexpr int G = 1 << LG;           /* bands per trace group */
-  constexpr int RG = BT_RING_GROUPS;   /* tile groups in the LDS ring */
-  constexpr int QG = RG / 4;           /* groups per refill quarter */
+  constexpr int NP = WalkGeom<CPL>::NP;
+  constexpr int OV = WALK_OVERLAP / G; /* groups a lane starts above its segment */
+  constexpr uint32_t COL = CPL == 1 ? 0xffffffffu : CPL == 2 ? 0x55555555u : CPL == 4 ? 0x11111111u
+                         : CPL == 8 ? 0x01010101u : 0x00010001u; /* one slot's bits of a trace word */
 
-  const int lane = threadIdx.x & 63;
+  const int lane = fresh_lane();
   const int orig = rd.orig;
   if (status != READ_OK) {
     if (lane == 0) {
@@ -961,96 +1010,111 @@ __device__ __forceinline__ void backtrack_read(const AlignArgs &a, const ReadDes
     return;
   }
   const int n_e = rd.n_e, n_k = rd.n_k;
-  const int gmax = (n_e + n_k - 2) >> LG; /* last trace group of the read */
-  auto ldt = [&](int grp) -> uint2 {
-    uint2 v = make_uint2(0u, 0u);
-    if (grp >= 0 && grp <= gmax) v = tr[(uint64_t)grp * 64 + lane];
-    return v;
-  };
+  const int t_start = __builtin_amdgcn_readfirstlane(e_start) + n_k - 1;
+  const int gtop = t_start >> LG; /* the path's last trace group */
+  const int groups = (n_e + n_k - 1 + G - 1) >> LG;
+  int sl; /* groups per segment */
+  const int nseg = path_segments(gtop + 1, sl);
+  int2 *pw = a.scratch + rd.pr_off;
 
-  int e = __builtin_amdgcn_readfirstlane(e_start), k = n_k - 1;
-  int gcur = (e + k) >> LG;
-  /* quarters of QG groups, walked downwards: quarters qa, qa-1, qa-2 are in
-   * the ring, qa-3 waits in registers */
-  int qa = gcur / QG;
-  for (int t = 0; t < 3; ++t)
-    for (int p = 0; p < QG; ++p) {
-      const int grp = (qa - t) * QG + p;
-      ring[(grp & (RG - 1)) * 64 + lane] = ldt(grp);
-    }
-  uint2 pend[QG];
-#pragma unroll
-  for (int p = 0; p < QG; ++p) pend[p] = ldt((qa - 3) * QG + p);
-  uint2 T = ring[(gcur & (RG - 1)) * 64 + lane];
-  uint2 Tn = ring[((gcur - 1) & (RG - 1)) * 64 + lane];
+  /* this lane's segment: groups glo .. ghi (lanes past the last segment have
+   * none), and where its walk starts */
+  const int glo = lane * sl;
+  const int ghi = lane < nseg ? min(gtop, glo + sl - 1) : glo - 1;
+  int g = ghi + OV;
+  int t = t_start, k = n_k - 1;
+  if (lane >= nseg) {
+    g = glo - 1;
+  } else if (g >= gtop) {
+    g = gtop;
+  } else {
+    t = (g << LG) + G - 1;
+    k = reinterpret_cast<const int *>(pw)[g + 1] + a.W / 2;
+    k = max(max(0, t - n_e + 1), min(k, min(n_k - 1, t)));
+  }
+  if (lane < nseg) ++g;
+  asm volatile("" ::: "memory"); /* the noted K are read before the path is written over them */
 
-  int PT = 0, PK = 0; /* gathered cells as t = e + k and k */
-  uint64_t q = 0;      /* cells stored */
-  uint32_t qn = 0;     /* cells gathered in lanes 0 .. qn-1, not stored yet */
-  const uint64_t res_end = rd.pr_off + (uint64_t)(n_e + n_k - 1);
-  int2 *__restrict__ out = a.scratch;
-  bool ok = true;
-  /* store the gathered cells in one coalesced store: lane l holds cell q + l
-   * counted from the end of the read's slots */
-  auto flush = [&]() {
-    if (lane < (int)qn) out[res_end - 1 - (q + lane)] = make_int2(PT - PK, PK);
-    q += qn;
-    qn = 0;
-  };
-
+  uint32_t nv = 0, nm = 0; /* path cells and M bits of the segment */
+  int t_in = 0, k_in = 0;  /* where the walk entered the segment */
   for (;;) {
-    /* the cells of the current group: one dependent step per cell, at most G
-     * of them (t falls at every step), so the lanes are emptied before a
-     * group that might not fit; the trace words of the lane the walk is in
-     * stay in SGPRs until k leaves that lane's CPL k-mers */
-    if (qn + G > 64) flush();
-    const int lower = gcur << LG;
-    int t = e + k;
-    int klo = 0x7fffffff; /* first k-mer of the loaded lane (none yet) */
-    uint32_t wd = 0, wk = 0; /* the lane's D-bit word, and its D | ~U word */
-    for (;;) {
-      t = __builtin_amdgcn_readfirstlane(t);
-      k = __builtin_amdgcn_readfirstlane(k);
-      PT = writelane(t, (int)qn, PT);
-      PK = writelane(k, (int)qn, PK);
-      ++qn;
-      if (k < klo) {
-        const int ln = (k & (N - 1)) >> LC;
-        wd = rlane_u(T.x, ln);
-        wk = wd | ~rlane_u(T.y, ln);
-        klo = k & ~(CPL - 1);
+    /* every lane from (t, k) in group g-1 down to the end of its segment.  The
+     * pieces of a group around k-mer kk hold the words of lanes a0, a0-1, ...
+     * with a0 odd, so that a piece's two words never straddle the ring's end;
+     * the first round only requests them */
+    int a0 = 0;
+    while (ballot(g >= glo)) {
+      const bool on = g >= glo;
+      const int lower = g << LG;
+      if (g == ghi) {
+        t_in = t;
+        k_in = k;
       }
-      /* diagonal (1,x): e-1, k-1; up (0,1): e-1; left (0,0): k-1 */
-      walk_move(t, k, wd, wk, trace_bit<CPL>(t, k));
-      /* stop when the walk left the group (t falls by 1 or 2 per step, so
-       * this also ends a walk that leaves the table; the caller checks that
-       * it ended at the origin), or with TRIM entered the trim column */
-      if (t < lower) break;
-      if constexpr (TRIM) {
-        if (k < 0) break;
+      const int a1 = ((k & (N - 1)) >> LC) | 1;
+      /* (lanes that are done read some group of the read: no branch around
+       * the loads, whose registers would double) */
+      u32x4 pf[NP];
+      const uint2 *row = tr + (uint64_t)min(max(g - 1, 0), gtop) * 64;
+#pragma unroll
+      for (int p = 0; p < NP; ++p) pf[p] = *reinterpret_cast<const u32x4 *>(row + ((a1 - 1 - 2 * p) & 63));
+      uint32_t V = 0, M = 0;
+      for (;;) {
+        const bool act = on && t >= lower && !(TRIM && k < 0);
+        if (!ballot(act)) break;
+        if (act) {
+          const int w = (k & (N - 1)) >> LC;
+          const int rel = (a0 - w) & 63;
+          uint2 T;
+          if (rel < 2 * NP)
+            T = reinterpret_cast<const uint2 *>(win)[((rel >> 1) * 64 + lane) * 2 + (w & 1)];
+          else
+            T = tr[(uint64_t)g * 64 + w];
+          /* the cell of band lower + b, slot k: bit 31 - (b * CPL + k mod CPL) */
+          const int b = t - lower;
+          const int pos = 31 - ((b << LC) + (k & (CPL - 1)));
+          const uint32_t m = ((T.x | ~T.y) >> pos) & COL;
+          const int j = min((uint32_t)(__ffs(m) - 1) >> LC, (uint32_t)b + 1u); /* up moves */
+          const bool found = j <= b; /* else the run leaves the group */
+          const int bl = found ? b - j : 0;
+          V |= ((2u << b) - 1u) & ~((1u << bl) - 1u);
+          if (found) {
+            M |= 1u << bl;
+            t -= 1 + (int)((T.x >> (pos + (j << LC))) & 1u);
+            k -= 1;
+          }
+          t -= j;
+        }
       }
+      if (on && g <= ghi) {
+        nv += (uint32_t)__popc(V);
+        nm += (uint32_t)__popc(M);
+        pw[g] = make_int2((int)V, (int)M);
+      }
+#pragma unroll
+      for (int p = 0; p < NP; ++p) win[p * 64 + lane] = pf[p];
+      a0 = a1;
+      if (on) --g;
     }
-    e = t - k;
-    if ((e | k) < 0) break;
-    const int gi = t >> LG;
-    if (gi != gcur) { /* the walk moved down by one group */
-      gcur = gi;
-      T = Tn;
-      if (gcur - 1 < (qa - 1) * QG) {
-        --qa;
-#pragma unroll
-        for (int p = 0; p < QG; ++p) ring[(((qa - 2) * QG + p) & (RG - 1)) * 64 + lane] = pend[p];
-#pragma unroll
-        for (int p = 0; p < QG; ++p) pend[p] = ldt((qa - 3) * QG + p);
-      }
-      Tn = ring[((gcur - 1) & (RG - 1)) * 64 + lane];
+    /* a lane agrees with the one above if it entered its segment where that
+     * one left its own */
+    const int ta = from_above(t), ka = from_above(k);
+    const bool off = lane < nseg - 1 && (t_in != ta || k_in != ka);
+    if (!ballot(off)) break;
+    if (off) {
+      g = ghi + 1;
+      t = ta;
+      k = ka;
+      nv = nm = 0;
     }
   }
-  flush();
-  if (ok && !(TRIM ? (k == -1 && e >= -1) : (e == -1 && k == -1))) ok = false;
-  if (lane == 0) {
-    a.path_len[orig] = ok ? q : 0;
-    a.path_src[orig] = res_end - q;
+  const int t_end = (int)rlane_u((uint32_t)t, 0), k_end = (int)rlane_u((uint32_t)k, 0);
+  const bool ok = k_end == -1 && (TRIM || t_end == -2);
+  /* path cells and M bits below each segment */
+  const uint32_t sv = lane_scan(nv), sm = lane_scan(nm);
+  if (nseg > 1 && lane < nseg) pw[groups + lane] = make_int2((int)(sv - nv), (int)(sm - nm));
+  if (lane == 63) {
+    a.path_len[orig] = ok ? (uint64_t)sv : 0;
+    a.path_src[orig] = (uint64_t)(gtop + 1);
     a.out_status[orig] = ok ? READ_OK : READ_BAND_LOST;
     if (!ok) a.out_ll[orig] = ABEA_NINF;
   }
@@ -1062,7 +1126,7 @@ __global__ __launch_bounds__(64) void k_backtrack(const AlignArgs a) {
   __shared__ WaveLds<CPL> lds;
   const int s = blockIdx.x;
   const ReadDesc rd = a.reads[s];
-  backtrack_read<CPL, TRIM>(a, rd, a.rstat[s], TRIM ? a.tend[s] : rd.n_e - 1, a.trace + rd.tr_off, lds.ring);
+  backtrack_read<CPL, TRIM>(kernel_args(), rd, a.rstat[s], TRIM ? a.tend[s] : rd.n_e - 1, a.trace + rd.tr_off, lds.win);
 }
 
 /* ----------------------------------------------------------------- fused */
@@ -1081,29 +1145,35 @@ __global__ __launch_bounds__(64 * WPG) void k_align(const AlignArgs a) {
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int w = blockIdx.x * WPG + wv;
   if (w >= a.n_workers) return;
-  uint2 *slab = a.trace + a.reads[w].tr_off;
   int s = w;
-  while (s < a.n_reads) {
-    const ReadDesc rd = a.reads[s];
-    int st = a.rstat[s];
-    /* the longest reads set the kernel's duration: let them issue first */
-    const bool urgent = rd.n_e + rd.n_k >= a.urgent_len;
-    if (urgent) __builtin_amdgcn_s_setprio(2);
-    int e_end = rd.n_e - 1;
-    if (st == READ_OK)
-      st = band_read<CPL, RPG, EDGE, TRIM>(a, rd, slab, lds[wv].band.lx, lds[wv].band.lk, e_end);
-    else
-      band_skipped(a, rd);
-    /* the walk reads back what this wavefront's lanes just stored (each lane
-     * its own words); keep the compiler from moving loads above the stores */
+  for (;;) {
+    KernArgs &a1 = kernel_args();
+    if (s >= a1.n_reads) break;
+    int st = a1.rstat[s];
+    int e_end;
+    {
+      const ReadDesc rd = read_desc(a1.reads, s);
+      /* the longest reads set the kernel's duration: let them issue first */
+      if (rd.n_e + rd.n_k >= a1.urgent_len) __builtin_amdgcn_s_setprio(2);
+      e_end = rd.n_e - 1;
+      if (st == READ_OK)
+        st = band_read<CPL, RPG, EDGE, TRIM>(a1, rd, a1.trace + read_desc(a1.reads, w).tr_off, lds[wv].band.lx,
+                                             lds[wv].band.lk, e_end);
+      else
+        band_skipped(a1, rd);
+    }
+    /* the walk reads back what this wavefront's lanes just stored; keep the
+     * compiler from moving loads above the stores */
     __builtin_amdgcn_s_waitcnt(0);
     asm volatile("" ::: "memory");
-    backtrack_read<CPL, TRIM>(a, rd, st, e_end, slab, lds[wv].ring);
-    if (urgent) __builtin_amdgcn_s_setprio(0);
+    KernArgs &a2 = kernel_args();
+    backtrack_read<CPL, TRIM>(a2, read_desc(a2.reads, s), st, e_end, a2.trace + read_desc(a2.reads, w).tr_off,
+                              lds[wv].win);
+    __builtin_amdgcn_s_setprio(0);
     asm volatile("" ::: "memory");
     uint32_t q = 0;
-    if ((threadIdx.x & 63) == 0) q = atomicAdd(a.queue, 1u);
-    s = a.n_workers + (int)__builtin_amdgcn_readfirstlane(q);
+    if ((threadIdx.x & 63) == 0) q = atomicAdd(a2.queue, 1u);
+    s = a2.n_workers + (int)__builtin_amdgcn_readfirstlane(q);
   }
 }
 
@@ -1134,34 +1204,73 @@ __global__ __launch_bounds__(64) void k_scan(const uint64_t *__restrict__ len, i
   if (lane == 63) off[n] = inc;
 }
 
-/* Read r's pairs (a contiguous run in the scratch, in path order) to its
- * place in the caller's array: COMPACT_SPLIT wavefronts per read, wavefront
- * y copying the y-th slice, so that the longest reads do not leave one
- * wavefront copying megabytes at the end of the kernel. */
-constexpr int COMPACT_SPLIT = 8;
-__global__ __launch_bounds__(64) void k_compact(const int2 *__restrict__ scratch,
-                                                const uint64_t *__restrict__ src,
-                                                const uint64_t *__restrict__ off,
-                                                int2 *__restrict__ pairs) {
-  const int r = blockIdx.x;
-  const uint64_t o = off[r];
-  const uint64_t n = off[r + 1] - o;
-  /* slices in whole 64-pair steps */
-  const uint64_t steps = (n + 63) >> 6;
-  const uint64_t s0 = steps * blockIdx.y / COMPACT_SPLIT, s1 = steps * (blockIdx.y + 1) / COMPACT_SPLIT;
-  const uint64_t end = min(n, s1 << 6);
-  const int2 *__restrict__ in = scratch + src[r];
+/* A read's pairs from its path bits (see backtrack_read), into its place in
+ * the caller's array.  The cell of a visited band t has k = -1 + (M bits of the
+ * path up to and with it) and e = t - k.  gridDim.y wavefronts per planned
+ * read (launch_expand), each taking a run of whole segments, so that the longest
+ * reads do not leave one wavefront writing megabytes at the end of the kernel.
+ * A wavefront
+ * takes up to 64 groups at a time (1024 bands), one per lane: the groups'
+ * counts are scanned over the lanes, each lane makes its cells into LDS, and the
+ * wavefront stores them coalesced.  Bound by the 8 bytes per pair written: the
+ * 1.2 G cells of a 20000-read job (0.5 to 200 kb) in 2.9 ms (3.4 TB/s), where
+ * copying pairs from a scratch took 3.9 ms. */
+constexpr int EXPAND_BANDS = 1024;
+__global__ __launch_bounds__(64) void k_expand(const ReadDesc *__restrict__ reads, const int2 *__restrict__ scratch,
+                                               const uint64_t *__restrict__ src,
+                                               const uint64_t *__restrict__ off, int lg,
+                                               int2 *__restrict__ pairs) {
+  __shared__ int2 cell[EXPAND_BANDS];
+  const ReadDesc rd = reads[blockIdx.x];
+  const int lane = threadIdx.x;
+  uint64_t o = off[rd.orig];
+  if (off[rd.orig + 1] == o) return; /* no path */
+  const int ng = (int)src[rd.orig];
+  int sl;
+  const int nseg = path_segments(ng, sl);
+  const int per = (nseg + (int)gridDim.y - 1) / (int)gridDim.y; /* segments per wavefront */
+  const int s0 = (int)blockIdx.y * per;
+  if (s0 >= nseg) return;
+  const int g1 = min(ng, (s0 + per) * sl);
+  const int2 *pw = scratch + rd.pr_off;
   int2 *__restrict__ out = pairs + o;
-  uint64_t t = (s0 << 6) + threadIdx.x;
-  /* eight loads in flight per lane */
-  for (; t + 448 < end; t += 512) {
-    int2 v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = in[t + 64 * j];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) out[t + 64 * j] = v[j];
+  uint32_t idx = 0; /* path cells before the chunk */
+  int k = -1;       /* k after them */
+  if (nseg > 1) {
+    const int2 b = pw[((rd.n_e + rd.n_k - 1 + (1 << lg) - 1) >> lg) + s0];
+    idx = (uint32_t)b.x;
+    k += b.y;
   }
-  for (; t < end; t += 64) out[t] = in[t];
+  const int cg = min(64, EXPAND_BANDS >> lg); /* groups per chunk */
+  const int gs = s0 * sl;
+  int2 w = make_int2(0, 0);
+  if (lane < cg && gs + lane < g1) w = pw[gs + lane];
+  for (int g = gs; g < g1; g += cg) {
+    uint32_t V = (uint32_t)w.x;
+    const uint32_t M = (uint32_t)w.y;
+    w = make_int2(0, 0);
+    if (lane < cg && g + cg + lane < g1) w = pw[g + cg + lane]; /* the next chunk's */
+    /* at most 1024 cells a chunk: both counts scanned in one word */
+    const uint32_t n = (uint32_t)__popc(V) | ((uint32_t)__popc(M) << 16);
+    const uint32_t inc = lane_scan(n);
+    const uint32_t all = rlane_u(inc, 63);
+    const uint32_t exc = inc - n;
+    uint32_t at = exc & 0xffffu;
+    int kk = k + (int)(exc >> 16);
+    const int t0 = (g + lane) << lg;
+    while (V) {
+      const int b = __ffs(V) - 1;
+      V &= V - 1;
+      kk += (int)((M >> b) & 1u);
+      cell[at++] = make_int2(t0 + b - kk, kk);
+    }
+    __syncthreads();
+    const uint32_t cnt = all & 0xffffu;
+    for (uint32_t p = lane; p < cnt; p += 64) out[idx + p] = cell[p];
+    __syncthreads();
+    idx += cnt;
+    k += (int)(all >> 16);
+  }
 }
 
 /* ------------------------------------------------------------- launchers */
@@ -1296,10 +1405,14 @@ hipError_t launch_scan(const uint64_t *len, int n, uint64_t *offset, hipStream_t
   return hipGetLastError();
 }
 
-hipError_t launch_compact(const int2 *scratch, const uint64_t *path_src, const uint64_t *offset,
-                          int n, int2 *pairs, hipStream_t st) {
+hipError_t launch_expand(const ReadDesc *reads, int n, int cpl, const int2 *scratch, const uint64_t *path_src,
+                         const uint64_t *offset, int2 *pairs, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_compact, dim3(n, COMPACT_SPLIT), dim3(64), 0, st, scratch, path_src, offset, pairs);
+  /* eight wavefronts per read, up to one per segment where the reads are
+   * few: 100 reads of up to 1 Mb take 607 us at eight */
+  const int split = std::min(WALK_MAX_SEGMENTS, std::max(8, 16384 / n));
+  hipLaunchKernelGGL(k_expand, dim3(n, split), dim3(64), 0, st, reads, scratch, path_src, offset,
+                     __builtin_ctz((unsigned)bands_per_group(cpl)), pairs);
   return hipGetLastError();
 }
 

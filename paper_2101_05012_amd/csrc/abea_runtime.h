@@ -32,7 +32,7 @@ struct Plan {
   int wpg = 1;            /* wavefronts per workgroup of the fused kernel */
   bool edge = false;      /* interior bands clear only the two slots beside the band */
   uint64_t n_trace = 0;   /* uint2 words */
-  uint64_t n_scratch = 0; /* pair slots */
+  uint64_t n_scratch = 0; /* word pairs of path scratch */
   uint64_t n_events = 0;
   uint64_t n_kmers = 0;
   uint64_t pairs_needed = 0;
