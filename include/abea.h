@@ -414,17 +414,16 @@ int abea_get_timings(abea_ctx *ctx, float *out, int n);
  * waves_per_group: wavefronts (reads) per workgroup of the fused kernel, 1, 2
  * or 4.  cells_per_lane: band slots per lane, 0 = the smallest power of two
  * with 64*c >= W + 2, else a power of two at least that and at most 16.
- * band_clear: which band slots the band fill resets to -inf after each band
- * whose cells all lie inside the DP table (every form gives the same
- * results; only the speed differs):
- *   ABEA_CLEAR_WINDOW : every slot outside the band's cells;
- *   ABEA_CLEAR_EDGES  : only the two slots beside the band (k-mers K-1 and
- *       K+W), the only ones the next two bands read; fewer vector and more
- *       scalar instructions per band, faster when the SIMDs hold several
- *       wavefronts, slower for a lone one; needs 2 or 4 cells_per_lane;
- *   ABEA_CLEAR_AUTO (0): edges at 4 cells_per_lane, and at 2 when the launch
- *       has at least two wavefronts per SIMD of the device (reads, or pool
- *       workers), else window.
+ * band_clear: the slot clearing that abea_get_plan_info reports.  It selects no
+ * kernel any more (results and speed are the same for each): at 2 and 4
+ * cells_per_lane bands whose cells all lie inside the DP table reset only the
+ * two slots beside the band (k-mers K-1 and K+W), at the others every slot
+ * outside it.
+ *   ABEA_CLEAR_WINDOW, ABEA_CLEAR_EDGES : reported as given (edges needs 2 or 4
+ *       cells_per_lane);
+ *   ABEA_CLEAR_AUTO (0): reported as edges at 4 cells_per_lane, and at 2 when
+ *       the launch has at least two wavefronts per SIMD of the device (reads,
+ *       or pool workers), else as window.
  * Bands with cells outside the table always clear every slot outside them.
  * Applies to later calls and graphs; waits for the context's queued work.
  * Errors: ABEA_E_INVAL.

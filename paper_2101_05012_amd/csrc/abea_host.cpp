@@ -172,19 +172,16 @@ void transitions(int64_t n_events, int64_t n_kmers, float *skip, float *stay, fl
 bool split_kernels(const abea_ctx *ctx) { return ctx->launch.workers == ABEA_WORKERS_SPLIT; }
 
 /* Wavefronts of the fused kernel that are resident at once on the device. */
-int resident_workers(abea_ctx *ctx, bool edge) {
-  const int gpc = align_groups_per_cu(ctx->cpl, refills_per_group(ctx->W, ctx->cpl), ctx->launch.waves_per_group,
-                                      edge, (ctx->flags & ABEA_F_TRIM) != 0, ctx->W);
+int resident_workers(abea_ctx *ctx) {
+  const int gpc = align_groups_per_cu(ctx->cpl, ctx->launch.waves_per_group, (ctx->flags & ABEA_F_TRIM) != 0, ctx->W);
   return std::max(1, gpc * ctx->num_cus * ctx->launch.waves_per_group);
 }
 
-/* Slot clearing of interior bands for a launch of `waves` wavefronts.  Edge
- * clearing trades per-band VALU work (every slot's window test) for scalar
- * work (two wave masks that follow the band); the scalar instructions cost a
- * lone wavefront more issue time than the vector ones they replace, and cost
- * less than them when other wavefronts on the SIMD keep the VALU busy.  At
- * four slots per lane it saves twice the vector work and wins either way; at
- * two it wins once the launch alone holds two wavefronts per SIMD. */
+/* The slot clearing that the plan reports for a launch of `waves` wavefronts
+ * (the rule of abea_launch_t).  It chooses no kernel: at two and four slots per
+ * lane one interior code, which clears the two edge slots, is the faster in every
+ * launch (a lone wavefront 90 ns per band against 109 for clearing the window,
+ * W = 100), and at the others every slot outside the band is cleared. */
 bool edge_clearing(const abea_ctx *ctx, int waves) {
   if (ctx->cpl != 2 && ctx->cpl != 4) return false;
   switch (ctx->launch.band_clear) {
@@ -248,7 +245,7 @@ int plan_batch(abea_ctx *ctx, Work &w, int n, const uint64_t *eo, const uint64_t
   int workers = n;
   const bool pool = !split && ctx->launch.workers > 0;
   P.edge = edge_clearing(ctx, pool ? std::min(n, ctx->launch.workers) : n);
-  if (pool) workers = std::min(n, std::min(ctx->launch.workers, resident_workers(ctx, P.edge)));
+  if (pool) workers = std::min(n, std::min(ctx->launch.workers, resident_workers(ctx)));
   if (!split && budget > 0) {
     uint64_t sum = 0;
     int fit = 0;
@@ -399,12 +396,12 @@ int enqueue_kernels(abea_ctx *ctx, Work &w, const DevIO &io, hipStream_t st, boo
       ap.reads = reads + P.parts[p];
       ap.rstat = rstat + P.parts[p];
       ap.n_reads = P.parts[p + 1] - P.parts[p];
-      HIP_TRY(ctx, launch_band(ap, P.cpl, refills_per_group(ctx->W, P.cpl), P.edge, st, p == 0 ? k0 : nullptr,
+      HIP_TRY(ctx, launch_band(ap, P.cpl, st, p == 0 ? k0 : nullptr,
                                p == np - 1 ? k1 : nullptr));
       if (p < np - 1) HIP_TRY(ctx, launch_backtrack(ap, P.cpl, st));
     }
   } else {
-    HIP_TRY(ctx, launch_align(a, P.cpl, refills_per_group(ctx->W, P.cpl), P.wpg, P.edge, st, k0, k1));
+    HIP_TRY(ctx, launch_align(a, P.cpl, P.wpg, st, k0, k1));
   }
   if (timed && !launched) { /* nothing dispatched: an empty interval */
     HIP_TRY(ctx, hipEventRecord(w.tev[2], st));

@@ -56,6 +56,14 @@ inline int refills_per_group(int W, int cpl) {
   if (band_shape_ok(W, cpl, 2)) return 2;
   return 0;
 }
+/* Refills per group of the interior bands of the edge kernels, whose slots hold
+ * k-mers from a multiple of cpl: the fewest of 1, 2 and 4 that fit, 0 if none. */
+inline int interior_refills(int W, int cpl) {
+  if (cpl != 2 && cpl != 4) return 0;
+  for (int rpg = 1; rpg <= 4; rpg <<= 1)
+    if (64 * cpl - W - (cpl - 1) >= bands_per_group(cpl) / rpg) return rpg;
+  return 0;
+}
 /* Slots per lane for a band width: the smallest power of two that fits. */
 inline int cells_per_lane(int W) {
   int c = 1;
@@ -141,16 +149,15 @@ hipError_t launch_prep(const ReadDesc *reads, int n_planned, const float *events
                        const float *shift, bool scale_events, float *xmean, uint32_t *krank,
                        int32_t *rstat, uint32_t *queue, hipStream_t st);
 /* t0, t1: null, or events that take the start and end time of the kernel's
- * own dispatch.  edge: interior bands clear only the two slots beside the
- * band (cpl 2 or 4), else every slot outside the band's cells */
-hipError_t launch_band(const AlignArgs &a, int cpl, int rpg, bool edge, hipStream_t st,
+ * own dispatch */
+hipError_t launch_band(const AlignArgs &a, int cpl, hipStream_t st,
                        hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 hipError_t launch_backtrack(const AlignArgs &a, int cpl, hipStream_t st);
 /* fused band + backtrack with a.n_workers wavefronts, wpg per workgroup */
-hipError_t launch_align(const AlignArgs &a, int cpl, int rpg, int wpg, bool edge, hipStream_t st,
+hipError_t launch_align(const AlignArgs &a, int cpl, int wpg, hipStream_t st,
                         hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 /* resident workgroups of the fused kernel per CU (occupancy) for band width W */
-int align_groups_per_cu(int cpl, int rpg, int wpg, bool edge, bool trim, int W);
+int align_groups_per_cu(int cpl, int wpg, bool trim, int W);
 hipError_t launch_scan(const uint64_t *len, int n, uint64_t *offset, hipStream_t st);
 /* dst[0, n) = src[0, n) by a kernel (src: the plan in mapped pinned host memory) */
 hipError_t launch_stage_plan(const ReadDesc *src, ReadDesc *dst, int n, hipStream_t st);

@@ -48,6 +48,7 @@
  * first maximum in the order diagonal, up, left.
  */
 #include "abea_internal.h"
+#include "abea_interior.h"
 
 #include <hip/hip_ext.h>
 
@@ -91,10 +92,18 @@ __device__ __forceinline__ float rlane(float v, int lane) {
 __device__ __forceinline__ uint32_t rlane_u(uint32_t v, int lane) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
 }
-/* per lane: bit set in `mask` selects if_set, else if_clear (one v_cndmask) */
+/* per lane: bit set in `mask`, made on the scalar unit, selects if_set, else
+ * if_clear (one v_cndmask) */
 __device__ __forceinline__ float sel(float if_clear, float if_set, uint64_t mask) {
   float r;
   asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(if_clear), "v"(if_set), "s"(mask));
+  return r;
+}
+/* the same for a mask that a vector compare made: two wait states first, which
+ * the compiler does not track into inline assembly */
+__device__ __forceinline__ float sel_cmp(float if_clear, float if_set, uint64_t mask) {
+  float r;
+  asm("s_nop 1\n\tv_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(if_clear), "v"(if_set), "s"(mask));
   return r;
 }
 /* a wave-uniform value held in a VGPR (one v_mov_b32) */
@@ -109,19 +118,20 @@ __device__ __forceinline__ float vmax3(float a, float b, float c) {
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
 }
-/* per lane: acc*2 + (bit of `mask`), one v_addc */
-__device__ __forceinline__ uint32_t shift_in(uint32_t acc, uint64_t mask) {
-  uint32_t r;
-  uint64_t co;
-  asm("v_addc_co_u32_e64 %0, %1, %2, %2, %3" : "=v"(r), "=s"(co) : "v"(acc), "s"(mask));
-  return r;
-}
-/* per lane: the bit of `mask`, the first bit of a new accumulator (one
- * v_cndmask, where a shift-in would need a zeroed register) */
-__device__ __forceinline__ uint32_t first_bit(uint64_t mask) {
-  uint32_t r;
-  asm("v_cndmask_b32_e64 %0, 0, 1, %1" : "=v"(r) : "s"(mask));
-  return r;
+/* per lane: acc*2 + (a == b), a compare and one v_addc.  In interior bands the
+ * compiler places them; elsewhere they stay together (the unrolled bands'
+ * compares would pile up in scalar registers), the two wait states between
+ * them included. */
+template <bool INTERIOR>
+__device__ __forceinline__ uint32_t shift_in_eq(uint32_t acc, float a, float b) {
+  if constexpr (INTERIOR) return acc + acc + (a == b ? 1u : 0u);
+  asm("v_cmp_eq_f32_e32 vcc, %1, %2\n\t"
+      "s_nop 1\n\t"
+      "v_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
+      : "+v"(acc)
+      : "v"(a), "v"(b)
+      : "vcc");
+  return acc;
 }
 __device__ __forceinline__ uint64_t ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
 /* lane `lane` of the result is `val` (uniform), the others keep `old`
@@ -228,19 +238,23 @@ __device__ __forceinline__ int fresh_lane() {
  * (`nfm` holds -FLT_MAX in every lane): then lo < hi holds exactly when lo is
  * -inf too (no finite lo is below -FLT_MAX), and every other outcome is
  * unchanged.  The compare runs on the VALU with all lanes active, so its lane
- * mask is all ones or all zeros and its low half is the result. */
+ * mask is all ones or all zeros and its low half is the result.  The s_nop
+ * gives the two wait states from the v_readlane of the end cells, which the
+ * compiler does not track into inline assembly. */
 template <bool ODD>
 __device__ __forceinline__ uint64_t sk_move_mask(int lo, int hi, float nfm) {
   float tv;
   uint64_t cm;
   if (ODD)
     asm volatile(
+        "s_nop 1\n\t"
         "v_max_f32 %[tv], %[h], %[nfm]\n\t"
         "v_cmp_lt_f32_e64 %[cm], %[lo], %[tv]"
         : [tv] "=&v"(tv), [cm] "=s"(cm)
         : [lo] "s"(lo), [h] "s"(hi), [nfm] "v"(nfm));
   else
     asm volatile(
+        "s_nop 1\n\t"
         "v_mov_b32 %[tv], %[h]\n\t"
         "v_cmp_lt_f32_e64 %[cm], %[lo], %[tv]"
         : [tv] "=&v"(tv), [cm] "=s"(cm)
@@ -258,33 +272,14 @@ __device__ __forceinline__ uint64_t sk_cmp_lane(int lo, float hv, float nfm) {
   uint64_t cm;
   if (ODD)
     asm volatile(
+        "s_nop 1\n\t"
         "v_max_f32 %[tv], %[h], %[nfm]\n\t"
         "v_cmp_lt_f32_e64 %[cm], %[lo], %[tv]"
         : [tv] "=&v"(tv), [cm] "=s"(cm)
         : [lo] "s"(lo), [h] "v"(hv), [nfm] "v"(nfm));
   else
-    asm volatile("v_cmp_lt_f32_e64 %[cm], %[lo], %[h]" : [cm] "=s"(cm) : [lo] "s"(lo), [h] "v"(hv));
+    asm volatile("s_nop 1\n\tv_cmp_lt_f32_e64 %[cm], %[lo], %[h]" : [cm] "=s"(cm) : [lo] "s"(lo), [h] "v"(hv));
   return cm;
-}
-
-/* The band move at two slots per lane with edge masks, from the lane
- * compare's mask cm: its bit hl (the last end cell's lane) goes straight into
- * SCC, and SCC moves the two edge masks one slot up, makes the move's wave
- * mask and adds the move to K (the shifted copy n0 of the top mask does not
- * depend on the move).  Returns the wave mask: all ones on a k-mer move. */
-__device__ __forceinline__ uint64_t sk_move_edges2(uint64_t cm, int hl, uint64_t (&m)[2], int &K) {
-  const uint64_t top = m[1];
-  const uint64_t n0 = (top << 1) | (top >> 63); /* the top register, one slot higher */
-  uint64_t mv;
-  asm("s_bitcmp1_b64 %[cm], %[hl]\n\t"
-      "s_cselect_b64 %[m1], %[m0], %[m1]\n\t"
-      "s_cselect_b64 %[m0], %[n0], %[m0]\n\t"
-      "s_cselect_b64 %[mv], -1, 0\n\t"
-      "s_addc_u32 %[K], %[K], 0"
-      : [m0] "+&s"(m[0]), [m1] "+&s"(m[1]), [mv] "=&s"(mv), [K] "+&s"(K)
-      : [cm] "s"(cm), [hl] "s"(hl), [n0] "s"(n0)
-      : "scc");
-  return mv;
 }
 
 /* The register of slot (.. % CPL == r) of every lane, as one VGPR. */
@@ -317,47 +312,10 @@ __device__ __forceinline__ int end_cell_bits4(const float (&v)[4], int slot) {
   return __builtin_amdgcn_readlane(__float_as_int(end_cell_reg4(v, slot)), slot >> 2);
 }
 
-/* Wave masks, one per register, of the two slots beside a band of W cells
- * whose first k-mer is K: k-mers K - 1 and K + W. */
-template <int CPL>
-__device__ __forceinline__ void edge_init(uint64_t (&m)[CPL], int K, int W) {
-  constexpr int N = 64 * CPL;
-  constexpr int LC = Log2<CPL>::v;
-  const int sa = (K - 1) & (N - 1), sb = (K + W) & (N - 1);
-#pragma unroll
-  for (int c = 0; c < CPL; ++c)
-    m[c] = (((sa & (CPL - 1)) == c) ? (1ull << (sa >> LC)) : 0ull) |
-           (((sb & (CPL - 1)) == c) ? (1ull << (sb >> LC)) : 0ull);
-}
-
-/* The same masks after the band move `mneg` (-1: k-mer move, the band and
- * both slots one k-mer higher; 0: unchanged).  One slot higher is the next
- * register of the same lane, or register 0 of the next lane (lane 63 wraps to
- * lane 0); the shifted copy does not depend on the move, so only the selects
- * wait for it. */
-template <int CPL>
-__device__ __forceinline__ void edge_move(uint64_t (&m)[CPL], int mneg) {
-  const uint64_t top = m[CPL - 1];
-  const uint64_t n0 = (top << 1) | (top >> 63); /* the top register, one slot higher */
-  /* 64-bit selects on one compare (the compiler would split each in two) */
-  if constexpr (CPL == 2) {
-    asm("s_cmp_lg_u32 %[mn], 0\n\t"
-        "s_cselect_b64 %[m1], %[m0], %[m1]\n\t"
-        "s_cselect_b64 %[m0], %[n0], %[m0]"
-        : [m0] "+&s"(m[0]), [m1] "+&s"(m[1])
-        : [n0] "s"(n0), [mn] "s"(mneg)
-        : "scc");
-  } else {
-    static_assert(CPL == 4, "edge masks are kept for two or four slots per lane");
-    asm("s_cmp_lg_u32 %[mn], 0\n\t"
-        "s_cselect_b64 %[m3], %[m2], %[m3]\n\t"
-        "s_cselect_b64 %[m2], %[m1], %[m2]\n\t"
-        "s_cselect_b64 %[m1], %[m0], %[m1]\n\t"
-        "s_cselect_b64 %[m0], %[n0], %[m0]"
-        : [m0] "+&s"(m[0]), [m1] "+&s"(m[1]), [m2] "+&s"(m[2]), [m3] "+&s"(m[3])
-        : [n0] "s"(n0), [mn] "s"(mneg)
-        : "scc");
-  }
+/* byte address in LDS of a shared array */
+template <typename T>
+__device__ __forceinline__ uint32_t lds_address(T *p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) T *)p;
 }
 
 /* Sizes of the band fill for CPL slots per lane.
@@ -425,11 +383,11 @@ struct WaveLds {
  * address + b (the event of a cell (e, k) in band i is i - 2 - k).
  *
  * Every slot computes a score each band; the slots outside the band must read
- * as -inf wherever a later cell of the band takes them as a neighbour.  Edge
- * bands (some cell outside the DP table) clear every slot outside the cells
- * of the band in the table, and so do interior bands unless CLEAR_EDGES.
- * With CLEAR_EDGES (two or four slots per lane) interior bands clear only
- * k-mers K - 1 and K + W: the cells of the next band read band i at
+ * as -inf wherever a later cell of the band takes them as a neighbour.  Bands
+ * with cells outside the DP table clear every slot outside the cells of the band
+ * in the table, and so do interior bands unless CLEAR_EDGES.  With CLEAR_EDGES
+ * (two or four slots per lane) interior bands run in abea_interior.h and clear
+ * only k-mers K - 1 and K + W: the cells of the next band read band i at
  * k-mers K' - 1 .. K' + W - 1 and band i - 1 at K' - 1 .. K' + W - 2, with K'
  * = K or K + 1, so no other slot outside a band is ever read by a cell in one,
  * and what those slots hold (scores of k-mers outside the band, or NaN from
@@ -438,12 +396,11 @@ struct WaveLds {
 template <int CPL, int RPG, int CLEAR, bool TRIM>
 __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 *trace,
                                          float *__restrict__ lx, float4 *__restrict__ lk, int &e_end) {
-  /* CLEAR: slot clearing of interior bands, 0 the window, 1 the two edge
-   * slots, 2 the two edge slots with W even at two slots per lane (then the
-   * band's first and last slots always lie in different registers) */
+  /* CLEAR: slot clearing of interior bands: 0 the window; else the two edge
+   * slots, 1 + W mod CPL (the interior code is written for each) */
   constexpr bool CLEAR_EDGES = CLEAR != 0;
-  constexpr bool W_EVEN = CLEAR == 2;
-  static_assert(!W_EVEN || CPL == 2, "the even-W form is for two slots per lane");
+  static_assert(!CLEAR_EDGES || CPL == 2 || CPL == 4, "edge clearing needs two or four slots per lane");
+  static_assert(CPL != 4 || Geom<CPL>::XS == EVENT_SUBRING, "the interior code knows the sub-rings' length");
   constexpr int N = Geom<CPL>::N;
   constexpr int LC = Geom<CPL>::LC;
   constexpr int G = Geom<CPL>::G;
@@ -453,20 +410,24 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
   constexpr int LS = Geom<CPL>::LS;
   constexpr int XS = Geom<CPL>::XS;
   constexpr int RXS = RX / S;
-  static_assert(S == 1 || (G % S == 0 && (G / RPG) % S == 0),
+  /* bands between slot refills; interior bands of edge kernels refill RPG times
+   * per group (every NB bands), the others at most twice */
+  constexpr int NB = G / RPG;
+  constexpr int RF = RPG > 2 ? G / 2 : NB;
+  static_assert(S == 1 || (G % S == 0 && RF % S == 0),
                 "refills at band offsets that are multiples of S keep each register's sub-ring fixed");
-  constexpr int RF = G / RPG; /* bands between slot refills (RPG refills per group) */
   static_assert(RF >= 2 && RF % 2 == 0, "refill interval must be an even band count");
 
   const int lane = fresh_lane();
   const int n_e = rd.n_e, n_k = rd.n_k;
   const int W = a.W;
 
-  const float lp_skip = rd.lp_skip, lp_stay = rd.lp_stay, lp_step = rd.lp_step;
-  /* vector copies of the skip and step constants: the moves of a register's
-   * first slot add them to a rotated neighbour, and only with a vector second
-   * operand can the rotation fold into the add (v_add_f32_dpp) */
-  const float lp_skip_v = to_vgpr(lp_skip), lp_step_v = to_vgpr(lp_step);
+  /* vector copies of the move constants: a SIMD starts two float adds,
+   * subtracts or multiplies of different waves per four cycles, but one whose
+   * operand is a scalar register holds it for all four (2.2 against 4.2 cycles
+   * an add with four waves per SIMD); and only with a vector second operand can
+   * a rotation fold into the add (v_add_f32_dpp) */
+  const float lp_skip = to_vgpr(rd.lp_skip), lp_stay = to_vgpr(rd.lp_stay), lp_step = to_vgpr(rd.lp_step);
   /* the read's event means, in place (every xstride-th float) or staged */
   const int xs = a.xstride;
   const float *__restrict__ xm = a.xsrc + (uint64_t)xs * rd.ev_off;
@@ -481,6 +442,10 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
   const float ksc = a.scale[rd.orig];
   const float ksh = a.shift[rd.orig];
   uint32_t bad_rank = 0; /* this lane met a rank outside the model */
+  /* 1 unless this is one of the longest reads, which run at raised priority (made
+   * here, or the compiler keeps it in a vector register) */
+  int calm;
+  asm("s_cmp_lt_i32 %1, %2\n\ts_cselect_b32 %0, 1, 0" : "=s"(calm) : "s"(n_e + n_k), "s"(a.urgent_len) : "scc");
   const int H = W / 2;
   const float NI = ABEA_NINF;
   const float NFM = __int_as_float((int)0xff7fffff); /* -FLT_MAX */
@@ -541,23 +506,10 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
   /* bits of the end cells of the latest band, for the next band's move:
    * band 1's are -inf, unless the trim cell is its first (W = 2, 3) */
   int lo_c = (trim && H == 1) ? __float_as_int(lp_trim) : ABEA_NINF_BITS, hi_c = ABEA_NINF_BITS;
-  /* edge kernels at two slots per lane keep the last end cell in its
-   * register (hv, lane hl) and decide the move by one compare against every
-   * lane; at four slots per lane (three or fewer wavefronts per SIMD) the
-   * longer scalar chain of that form did not pay */
-  constexpr bool LANE_MOVE = CLEAR_EDGES && CPL == 2;
-  float hv = NI;
-  int hl = 0;
-  /* CLEAR_EDGES: interior bands clear only the two slots beside the band,
-   * whose wave masks follow every band move on the SALU */
-  static_assert(!CLEAR_EDGES || CPL == 2 || CPL == 4, "edge clearing needs two or four slots per lane");
-  constexpr bool EDGE_MASKS = CLEAR_EDGES;
-  uint64_t edge[CPL];
-  if constexpr (EDGE_MASKS) edge_init<CPL>(edge, K, W);
-  /* at two slots per lane: all ones when the first (last) slot of the latest
-   * band is odd, i.e. in register 1 */
-  uint64_t plo = (K & 1) ? ~0ull : 0ull;
-  uint64_t phi = ((K + W - 1) & 1) ? ~0ull : 0ull; /* ~plo when W is even */
+  /* edge kernels: the next band's move (1: a k-mer move), and its rotated
+   * neighbours, moved */
+  int mv_n = 0;
+  float lf_n = NI, dg_n = NI;
   float Spp[CPL], Sp[CPL], PM[CPL], PC[CPL], PH[CPL];
   int kvs[CPL]; /* kv(slot), the k-mer the slot holds */
   int xb[CPL]; /* ring index of the slot's event at band b = 0 of the group */
@@ -570,6 +522,8 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
     kvs[c] = kv;
     xb[c] = 0;
   }
+
+  if constexpr (CLEAR_EDGES) add_rot2(Sp[CPL - 1], lp_skip, Spp[CPL - 1], lp_step, lf_n, dg_n);
 
   /* Rings: event e in sub-ring e mod S at entry (e / S) mod (RX / S), k-mer
    * k at lk[k mod RK], written a quarter (64 entries) at a time; the quarter
@@ -642,7 +596,7 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
   auto band = [&](auto interior_tag, float(&Spp)[CPL], const float(&Sp)[CPL], int i, int b,
                   const float(&X)[CPL], bool fresh) {
     constexpr bool INTERIOR = decltype(interior_tag)::value;
-    constexpr bool EDGE = INTERIOR && EDGE_MASKS;
+    static_assert(!(INTERIOR && CLEAR_EDGES), "edge kernels run interior bands in abea_interior.h");
     /* the band position is wave-uniform: keep it in SGPRs */
     K = __builtin_amdgcn_readfirstlane(K);
     /* Suzuki-Kasahara placement from the two end cells of band i-1 (taken
@@ -650,25 +604,11 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
      * when b is.  The event of the first cell follows from K: e + k = i - 2
      * in band i. */
     const int lo = lo_c, hi = hi_c;
-    uint64_t mv;
-    if constexpr (LANE_MOVE) {
-      static_assert(EDGE_MASKS && CPL == 2, "the lane-compare move keeps two-slot edge masks");
-      /* the previous band of an interior band lies wholly inside the table,
-       * so both its end cells are finite (each of its cells has its up or
-       * left neighbour in the band before): the alternation for two -inf
-       * end cells never applies, and odd bands compare as even ones */
-      const uint64_t cm = ((b & 1) && !INTERIOR) ? sk_cmp_lane<true>(lo, hv, NFM) : sk_cmp_lane<false>(lo, hv, NFM);
-      mv = sk_move_edges2(cm, __builtin_amdgcn_readfirstlane(hl), edge, K);
+    if constexpr (CLEAR_EDGES) {
+      K = __builtin_amdgcn_readfirstlane(K + mv_n);
     } else {
-      mv = (b & 1) ? sk_move_mask<true>(lo, hi, NFM) : sk_move_mask<false>(lo, hi, NFM);
-      const int mneg = __builtin_amdgcn_readfirstlane((int)(uint32_t)mv);
-      K -= mneg;
-      if constexpr (EDGE_MASKS) edge_move<CPL>(edge, mneg);
-    }
-    if constexpr (CPL == 2) {
-      /* a k-mer move changes the parity of both end slots */
-      plo ^= mv;
-      if constexpr (!W_EVEN) phi ^= mv;
+      const uint64_t mv = (b & 1) ? sk_move_mask<true>(lo, hi, NFM) : sk_move_mask<false>(lo, hi, NFM);
+      K -= __builtin_amdgcn_readfirstlane((int)(uint32_t)mv);
     }
 
     /* cells of band i inside the band and the table: k-mers kv with
@@ -684,8 +624,8 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
     /* slot s-1 of a register's first slot is the last register of lane l-1:
      * left (e, k-1) in band i-1 and diag (e-1, k-1) in band i-2, each with
      * its move's constant added */
-    float lf0, dg0;
-    add_rot2(Sp[CPL - 1], lp_skip_v, Spp[CPL - 1], lp_step_v, lf0, dg0);
+    float lf0 = lf_n, dg0 = dg_n;
+    if constexpr (!CLEAR_EDGES) add_rot2(Sp[CPL - 1], lp_skip, Spp[CPL - 1], lp_step, lf0, dg0);
     float nv[CPL]; /* band i; band i-2 is still read below */
     float sv[CPL]; /* band i before the window mask */
     /* trim, in bands with cells outside the table: the first k-mer takes no
@@ -712,7 +652,7 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
       const float su = (up + lp_stay) + em;
       float sl = lsk;
       if constexpr (!INTERIOR && TRIM) {
-        if (no_skip_in) sl = sel(sl, NI, ballot(kvs[c] == 0));
+        if (no_skip_in) sl = sel_cmp(sl, NI, ballot(kvs[c] == 0));
       }
       /* first maximum in the order D, U, L.  The value is the plain maximum
        * (scores are finite or -inf, never NaN or -0, so v_max3 gives the
@@ -721,28 +661,13 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
        * su is; otherwise L.  The compares stay off the chain from one band
        * to the next */
       sv[c] = vmax3(sd, su, sl);
-      const uint64_t md = ballot(sv[c] == sd);
-      const uint64_t mu = ballot(sv[c] == su);
-      if constexpr (EDGE) {
-        /* only the two slots beside the band are cleared: the next two bands
-         * read no other slot outside this band (the others may hold any
-         * value, the scores of k-mers outside the band) */
-        nv[c] = sel(sv[c], NI, edge[c]);
-      } else {
-        const uint64_t valid = ballot((uint32_t)(kvs[c] - wlo) < (uint32_t)wlen);
-        nv[c] = sel(NI, sv[c], valid);
-        if constexpr (!INTERIOR && TRIM) {
-          if (trim_cell) nv[c] = sel(nv[c], up + lp_trim, ballot(kvs[c] == -1));
-        }
+      nv[c] = (uint32_t)(kvs[c] - wlo) < (uint32_t)wlen ? sv[c] : NI;
+      if constexpr (!INTERIOR && TRIM) {
+        if (trim_cell) nv[c] = sel_cmp(nv[c], up + lp_trim, ballot(kvs[c] == -1));
       }
       /* trace planes: the D bit, and the U bit (read only when D is clear) */
-      if (fresh && c == 0) {
-        TD = first_bit(md);
-        TU = first_bit(mu);
-      } else {
-        TD = shift_in(TD, md);
-        TU = shift_in(TU, mu);
-      }
+      TD = shift_in_eq<INTERIOR>(fresh && c == 0 ? 0u : TD, sv[c], sd);
+      TU = shift_in_eq<INTERIOR>(fresh && c == 0 ? 0u : TU, sv[c], su);
     }
     /* the end cells of this band for the next band's move.  Both lie in the
      * band; inside the table they are never masked, so they are read from
@@ -752,16 +677,21 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
       const float(&src)[CPL] = INTERIOR ? sv : nv;
       const int sf = K & (N - 1);
       const int sh = (K + W - 1) & (N - 1);
-      if constexpr (CPL == 2) {
-        /* register of each end slot from its parity, as wave masks kept on
-         * the SALU */
-        lo_c = __builtin_amdgcn_readlane(__float_as_int(sel(src[0], src[1], plo)), sf >> LC);
-        if constexpr (LANE_MOVE) {
-          hv = W_EVEN ? sel(src[1], src[0], plo) : sel(src[0], src[1], phi);
-          hl = sh >> LC;
+      if constexpr (CLEAR_EDGES) {
+        float r, h;
+        if constexpr (CPL == 2) {
+          r = sel(src[0], src[1], (sf & 1) ? ~0ull : 0ull);
+          h = sel(src[0], src[1], (sh & 1) ? ~0ull : 0ull);
         } else {
-          hi_c = __builtin_amdgcn_readlane(__float_as_int(sel(src[0], src[1], phi)), sh >> LC);
+          r = end_cell_reg4(src, sf);
+          h = end_cell_reg4(src, sh);
         }
+        /* the next band is odd, and outside the table, if this one is even:
+         * the last end cell raised to -FLT_MAX (see sk_move_mask) */
+        const int lo1 = __builtin_amdgcn_readlane(__float_as_int(r), sf >> LC);
+        const uint64_t cm = (b & 1) ? sk_cmp_lane<false>(lo1, h, NFM) : sk_cmp_lane<true>(lo1, h, NFM);
+        mv_n = __builtin_amdgcn_readfirstlane((int)(cm >> (sh >> LC)) & 1);
+        add_rot2(nv[CPL - 1], lp_skip, Sp[CPL - 1], lp_step, lf_n, dg_n);
       } else if constexpr (CPL == 4) {
         lo_c = end_cell_bits4(src, sf);
         hi_c = end_cell_bits4(src, sh);
@@ -822,64 +752,150 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
     }
   };
 
+  /* nb bands from band i, the first of a group, a pair at a time (not unrolled:
+   * edge kernels run only bands with cells outside the table here, and their
+   * registers stay with the interior code). */
+  auto few_bands = [&](int i, int nb) {
+    float xa[2][CPL], xn[2][CPL];
+    TD = 0;
+    TU = 0;
+    refill(i, 0);
+    load_x(xa[0], 0);
+    load_x(xa[1], 1);
+#pragma nounroll
+    for (int b = 0;;) {
+      load_x(xn[0], b + 2);
+      load_x(xn[1], b + 3);
+      band(std::false_type(), Spp, Sp, i + b, 0, xa[0], false);
+      if (b + 1 == nb) break;
+      band(std::false_type(), Sp, Spp, i + b + 1, 1, xa[1], false);
+      b += 2;
+      if (b == nb) break;
+      if (b % RF == 0) {
+        refill(i + b, b);
+        load_x(xa[0], b);
+        load_x(xa[1], b + 1);
+      } else {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int c = 0; c < CPL; ++c) xa[q][c] = xn[q][c];
+      }
+    }
+  };
+
+  /* An interior group of an edge kernel: RPG refill intervals.  In each a lane's
+   * slots hold CPL consecutive k-mers kv0 .. kv0+CPL-1 from a multiple of CPL: the
+   * one K lies in, or a higher one (64*CPL - W - (CPL-1) >= NB keeps the k-mers
+   * 64*CPL higher out of the band meanwhile).  kv0's parameters and the event of
+   * the last of them at the interval's first band are all the lane needs. */
+  auto interior_group = [&](int i) {
+    if constexpr (CLEAR_EDGES) {
+      Interior<CPL> v;
+      v.stay = lp_stay;
+      v.skip = lp_skip;
+      v.step = lp_step;
+      v.calm = calm;
+      v.td = TD; /* a group's bits fill the words: nothing of these remains */
+      v.tu = TU;
+      v.lf = lf_n;
+      v.dg = dg_n;
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) {
+        v.p[c] = Spp[c];
+        v.q[c] = Sp[c];
+      }
+      const uint32_t bx = lds_address(lx), bk = lds_address(lk);
+      auto interval = [&](auto res_tag, int ib) {
+        constexpr int RES = decltype(res_tag)::value;
+        const int kv0 = (K & -CPL) + ((lane * CPL - (K & -CPL)) & (N - 1));
+        v.ak = bk + 16u * (uint32_t)(kv0 & (RK - 1));
+        v.ax = bx + 4u * (uint32_t)(((ib - 2 - (kv0 + CPL - 1)) >> LS) & (RXS - 1));
+        v.K = __builtin_amdgcn_readfirstlane(K + mv_n);
+        if constexpr (CPL == 2)
+          interior<NB, CLEAR - 1>(v, W);
+        else
+          interior<NB, CLEAR - 1, RES>(v, W);
+        K = __builtin_amdgcn_readfirstlane(v.K);
+        mv_n = __builtin_amdgcn_readfirstlane(v.mv);
+      };
+#pragma unroll
+      for (int b = 0; b < G; b += NB) {
+        if constexpr (CPL == 4 && NB == 2) {
+          if (b & 2)
+            interval(std::integral_constant<int, 3>(), i + b);
+          else
+            interval(std::integral_constant<int, 1>(), i + b);
+        } else {
+          interval(std::integral_constant<int, 1>(), i + b);
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) {
+        Spp[c] = v.p[c];
+        Sp[c] = v.q[c];
+      }
+      TD = v.td;
+      TU = v.tu;
+      lf_n = v.lf;
+      dg_n = v.dg;
+    } else {
+      group(std::true_type(), i);
+    }
+  };
+
   /* Full groups of G bands (band i = 2 + t, group t / G): ring refill and
    * interior test once per group, one trace word per lane per group. */
   int i = 2;
   uint64_t g = 0;
-  /* K at the start of each group, for the walk (64 groups gathered in lanes,
-   * then one coalesced store), in the read's path scratch, which the walk
-   * fills only after it has read them */
-  int kgat = 0;
+  /* K at the start of each group, for the walk (every lane stores the same
+   * word), in the read's path scratch, which the walk fills only after it has
+   * read them */
   int *__restrict__ kpos = reinterpret_cast<int *>(a.scratch + rd.pr_off);
-  auto note_k = [&]() {
-    kgat = writelane(K, (int)g & 63, kgat);
-    if (((int)g & 63) == 63) kpos[(g & ~63ull) + lane] = kgat;
-  };
   const bool gap_ok = N - W >= CPL; /* interior bands clear CPL slots outside the band */
   while (i + G - 1 <= last) {
     K = __builtin_amdgcn_readfirstlane(K);
-    note_k();
     E = i - 3 - K; /* band i - 1 is the latest */
-    advance_rings();
     /* with trim the last k-mer stays out of interior bands, whose cells the
-     * end recurrence does not read */
-    const bool interior = gap_ok & (K >= 0) & (E >= W - 1) & (E + G <= n_e - 1) &
-                          (K + G + W - 1 <= n_k - 1 - (int)trim);
-    if (interior) {
-      group(std::true_type(), i);
-      cells += (uint64_t)W * G;
+     * end recurrence does not read.  A group moves K and E up by G together, so
+     * the next n groups are interior whatever their moves */
+    int n = 0;
+    if (gap_ok & (K >= 0) & (E >= W - 1)) n = min(n_e - 1 - E, n_k - 1 - (int)trim - (K + W - 1)) / G;
+    if (n > 0) {
+      cells += (uint64_t)W * (uint64_t)(G * n);
+      do {
+        E = i - 3 - K;
+        advance_rings();
+        kpos[g] = K;
+        interior_group(i);
+        trace[g * 64 + lane] = make_uint2(TD, TU);
+        ++g;
+        i += G;
+      } while (--n > 0);
     } else {
-      group(std::false_type(), i);
+      advance_rings();
+      kpos[g] = K;
+      if constexpr (CLEAR_EDGES)
+        few_bands(i, G);
+      else
+        group(std::false_type(), i);
+      trace[g * 64 + lane] = make_uint2(TD, TU);
+      ++g;
+      i += G;
     }
-    trace[g * 64 + lane] = make_uint2(TD, TU);
-    ++g;
-    i += G;
   }
   /* the last, partial group */
   if (i <= last) {
     K = __builtin_amdgcn_readfirstlane(K);
-    note_k();
     E = i - 3 - K;
     advance_rings();
+    kpos[g] = K;
     const int gb = last - i + 1;
-    TD = 0;
-    TU = 0;
-    for (int b = 0;; b += 2) {
-      if (b % RF == 0) refill(i + b, b);
-      float x0[CPL], x1[CPL];
-      load_x(x0, b);
-      load_x(x1, b + 1);
-      band(std::false_type(), Spp, Sp, i + b, b, x0, false);
-      if (i + b + 1 > last) break;
-      band(std::false_type(), Sp, Spp, i + b + 1, b + 1, x1, false);
-      if (i + b + 2 > last) break;
-    }
+    few_bands(i, gb);
     i = last + 1;
     const int sh = (G - gb) * CPL;
     trace[g * 64 + lane] = make_uint2(TD << sh, TU << sh);
-    ++g;
   }
-  if (lane < ((int)g & 63)) kpos[(g & ~63ull) + lane] = kgat;
 
   /* terminal cell (n_e-1, n_k-1) is in the last band if its k-mer is; with
    * trim the end cell the end recurrence chose */
@@ -923,7 +939,7 @@ template <int CPL, int RPG, int EDGE, bool TRIM>
 __global__ __launch_bounds__(64) void k_band(const AlignArgs a) {
   __shared__ WaveLds<CPL> lds;
   const int s = blockIdx.x;
-  const ReadDesc rd = a.reads[s];
+  const ReadDesc rd = read_desc(a.reads, s);
   if (a.rstat[s] != READ_OK) {
     band_skipped(kernel_args(), rd);
     return;
@@ -1108,7 +1124,7 @@ __device__ __forceinline__ void backtrack_read(KernArgs &a, const ReadDesc &rd, 
     }
   }
   const int t_end = (int)rlane_u((uint32_t)t, 0), k_end = (int)rlane_u((uint32_t)k, 0);
-  const bool ok = k_end == -1 && (TRIM || t_end == -2);
+  const bool ok = k_end == -1 && (TRIM ? t_end >= -2 : t_end == -2);
   /* path cells and M bits below each segment */
   const uint32_t sv = lane_scan(nv), sm = lane_scan(nm);
   if (nseg > 1 && lane < nseg) pw[groups + lane] = make_int2((int)(sv - nv), (int)(sm - nm));
@@ -1125,11 +1141,18 @@ template <int CPL, bool TRIM>
 __global__ __launch_bounds__(64) void k_backtrack(const AlignArgs a) {
   __shared__ WaveLds<CPL> lds;
   const int s = blockIdx.x;
-  const ReadDesc rd = a.reads[s];
+  const ReadDesc rd = read_desc(a.reads, s);
   backtrack_read<CPL, TRIM>(kernel_args(), rd, a.rstat[s], TRIM ? a.tend[s] : rd.n_e - 1, a.trace + rd.tr_off, lds.win);
 }
 
 /* ----------------------------------------------------------------- fused */
+
+/* Wavefronts per SIMD that the fused kernel's registers must leave room for
+ * (the compiler would take more registers for the bands at the table's edges,
+ * which are few). */
+constexpr int waves_per_simd(int cpl, bool trim) {
+  return cpl == 1 ? (trim ? 4 : 5) : cpl == 2 ? 5 : cpl == 4 ? 4 : cpl == 8 ? 2 : 1;
+}
 
 /* Band fill and backtrack of a read by one wavefront, with a device work
  * queue.  Worker w (wavefront w of the grid, w < n_workers) first aligns
@@ -1140,7 +1163,7 @@ __global__ __launch_bounds__(64) void k_backtrack(const AlignArgs a) {
  * plain one-launch form; fewer workers bound the trace memory (admission by
  * traceback bytes) and let the longest reads of the batch overlap the rest. */
 template <int CPL, int RPG, int WPG, int EDGE, bool TRIM>
-__global__ __launch_bounds__(64 * WPG) void k_align(const AlignArgs a) {
+__global__ __launch_bounds__(64 * WPG, waves_per_simd(CPL, TRIM)) void k_align(const AlignArgs a) {
   __shared__ WaveLds<CPL> lds[WPG];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int w = blockIdx.x * WPG + wv;
@@ -1287,30 +1310,44 @@ hipError_t launch_prep(const ReadDesc *reads, int n_planned, const float *events
   return hipGetLastError();
 }
 
-/* Kernel variant for (cells per lane, refills per group, edge clearing). */
-/* the third argument is the clearing form (band_read's CLEAR); w_odd is the
- * parity of W */
-#define ABEA_VARIANTS(CALL)                                          \
-  if (cpl == 1 && rpg == 1 && !edge) CALL(1, 1, 0);                  \
-  if (cpl == 1 && rpg == 2 && !edge) CALL(1, 2, 0);                  \
-  if (cpl == 2 && rpg == 1 && !edge) CALL(2, 1, 0);                  \
-  if (cpl == 2 && rpg == 2 && !edge) CALL(2, 2, 0);                  \
-  if (cpl == 2 && rpg == 1 && edge && w_odd) CALL(2, 1, 1);          \
-  if (cpl == 2 && rpg == 2 && edge && w_odd) CALL(2, 2, 1);          \
-  if (cpl == 2 && rpg == 1 && edge && !w_odd) CALL(2, 1, 2);         \
-  if (cpl == 2 && rpg == 2 && edge && !w_odd) CALL(2, 2, 2);         \
-  if (cpl == 4 && rpg == 1 && !edge) CALL(4, 1, 0);                  \
-  if (cpl == 4 && rpg == 2 && !edge) CALL(4, 2, 0);                  \
-  if (cpl == 4 && rpg == 1 && edge) CALL(4, 1, 1);                   \
-  if (cpl == 4 && rpg == 2 && edge) CALL(4, 2, 1);                   \
-  if (cpl == 8 && rpg == 1 && !edge) CALL(8, 1, 0);                  \
-  if (cpl == 8 && rpg == 2 && !edge) CALL(8, 2, 0);                  \
-  if (cpl == 16 && rpg == 1 && !edge) CALL(16, 1, 0);
+/* Kernel variants: (slots per lane, refills per group, CLEAR of band_read).  At
+ * two and four slots per lane the kernels run interior bands in abea_interior.h,
+ * ec = 1 + W mod cpl; where its refill intervals do not fit (W = 252 at four: see
+ * interior_refills), and at other slot counts, the window kernels run (ec = 0). */
+#define ABEA_VARIANTS(CALL)                             \
+  if (cpl == 1 && rpg == 1 && !ec) CALL(1, 1, 0);       \
+  if (cpl == 1 && rpg == 2 && !ec) CALL(1, 2, 0);       \
+  if (cpl == 2 && rpg == 1 && ec == 1) CALL(2, 1, 1);   \
+  if (cpl == 2 && rpg == 1 && ec == 2) CALL(2, 1, 2);   \
+  if (cpl == 2 && rpg == 2 && ec == 1) CALL(2, 2, 1);   \
+  if (cpl == 2 && rpg == 2 && ec == 2) CALL(2, 2, 2);   \
+  if (cpl == 2 && rpg == 4 && ec == 1) CALL(2, 4, 1);   \
+  if (cpl == 4 && rpg == 1 && ec == 1) CALL(4, 1, 1);   \
+  if (cpl == 4 && rpg == 1 && ec == 2) CALL(4, 1, 2);   \
+  if (cpl == 4 && rpg == 1 && ec == 3) CALL(4, 1, 3);   \
+  if (cpl == 4 && rpg == 1 && ec == 4) CALL(4, 1, 4);   \
+  if (cpl == 4 && rpg == 2 && ec == 0) CALL(4, 2, 0);   \
+  if (cpl == 4 && rpg == 2 && ec == 1) CALL(4, 2, 1);   \
+  if (cpl == 4 && rpg == 2 && ec == 2) CALL(4, 2, 2);   \
+  if (cpl == 4 && rpg == 2 && ec == 3) CALL(4, 2, 3);   \
+  if (cpl == 4 && rpg == 2 && ec == 4) CALL(4, 2, 4);   \
+  if (cpl == 4 && rpg == 4 && ec == 3) CALL(4, 4, 3);   \
+  if (cpl == 4 && rpg == 4 && ec == 4) CALL(4, 4, 4);   \
+  if (cpl == 8 && rpg == 1 && !ec) CALL(8, 1, 0);       \
+  if (cpl == 8 && rpg == 2 && !ec) CALL(8, 2, 0);       \
+  if (cpl == 16 && rpg == 1 && !ec) CALL(16, 1, 0);
 
-hipError_t launch_band(const AlignArgs &a, int cpl, int rpg, bool edge, hipStream_t st, hipEvent_t t0,
+static void variant(int cpl, int W, int &rpg, int &ec) {
+  rpg = interior_refills(W, cpl);
+  ec = rpg > 0 ? 1 + W % cpl : 0;
+  if (rpg == 0) rpg = refills_per_group(W, cpl);
+}
+
+hipError_t launch_band(const AlignArgs &a, int cpl, hipStream_t st, hipEvent_t t0,
                        hipEvent_t t1) {
   if (a.n_reads <= 0) return hipSuccess;
-  const bool w_odd = (a.W & 1) != 0;
+  int rpg, ec;
+  variant(cpl, a.W, rpg, ec);
 #define ABEA_L(C, R, E)                                                                                 \
   {                                                                                                     \
     if (a.trim)                                                                                         \
@@ -1355,11 +1392,12 @@ static hipError_t launch_align_c(const AlignArgs &a, int wpg, hipStream_t st, hi
   return hipGetLastError();
 }
 
-hipError_t launch_align(const AlignArgs &a, int cpl, int rpg, int wpg, bool edge, hipStream_t st,
+hipError_t launch_align(const AlignArgs &a, int cpl, int wpg, hipStream_t st,
                         hipEvent_t t0, hipEvent_t t1) {
   if (a.n_reads <= 0 || a.n_workers <= 0) return hipSuccess;
   if (a.n_workers > a.n_reads) return hipErrorInvalidValue;
-  const bool w_odd = (a.W & 1) != 0;
+  int rpg, ec;
+  variant(cpl, a.W, rpg, ec);
 #define ABEA_L(C, R, E)                                                                                       \
   return a.trim ? launch_align_c<C, R, E, true>(a, wpg, st, t0, t1) : launch_align_c<C, R, E, false>(a, wpg, st, t0, t1)
   ABEA_VARIANTS(ABEA_L)
@@ -1379,8 +1417,9 @@ static int groups_per_cu_c(int wpg) {
   return e == hipSuccess ? n : 0;
 }
 
-int align_groups_per_cu(int cpl, int rpg, int wpg, bool edge, bool trim, int W) {
-  const bool w_odd = (W & 1) != 0;
+int align_groups_per_cu(int cpl, int wpg, bool trim, int W) {
+  int rpg, ec;
+  variant(cpl, W, rpg, ec);
 #define ABEA_L(C, R, E) return trim ? groups_per_cu_c<C, R, E, true>(wpg) : groups_per_cu_c<C, R, E, false>(wpg)
   ABEA_VARIANTS(ABEA_L)
 #undef ABEA_L
