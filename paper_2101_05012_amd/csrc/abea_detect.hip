@@ -24,11 +24,10 @@
  *
  * The work is a stream over the raw samples:
  *   k_ed_tiles     the tile table (one wavefront per read);
- *   k_ed_detect    one workgroup per tile of 1024 boundaries of one read:
- *                  samples to LDS as prefix sums, both statistics, peaks
- *                  (four consecutive boundaries per thread, their window
- *                  maxima shared), one bit per boundary, and the tile's
- *                  event count and first change point;
+ *   k_ed_detect    one wavefront per tile of 1024 boundaries of one read: both
+ *                  statistics, peaks, one bit per boundary, and the tile's
+ *                  event count and first change point (k_ed_detect_any, a
+ *                  workgroup per tile, for windows other than 3 and 8);
  *   k_ed_scan      exclusive scan of the tile counts, per 1024 tiles, then
  *                  over the blocks (k_ed_scan_top);
  *   k_ed_events    one workgroup per tile: the tile's event starts in order,
@@ -117,86 +116,24 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
   return r;
 }
 
-/* largest of v[i0 .. i0+cnt-1] and init (cnt >= 0, compile-time indices) */
-template <int I0, int CNT, int NV>
-__device__ __forceinline__ float run_max(const float (&v)[NV], float init) {
-  float m = init;
-  int i = I0;
-#pragma unroll
-  for (; i + 1 < I0 + CNT; i += 2) m = max3(m, v[i], v[i + 1]);
-  if constexpr ((CNT & 1) != 0) m = max2(m, v[I0 + CNT - 1]);
-  return m;
-}
-
-/* Peaks of the detector (window W, thr = t^2) at the four boundaries
+/* Peaks of the detector (window w, thr = t^2) at the four boundaries
  * ts[q0 .. q0+3]: boundary q is a peak if ts[q] is above thr and above every
- * statistic up to W-1 before it, and not below any up to W-1 after it.
+ * statistic up to w-1 before it, and not below any up to w-1 after it.
  * Undefined boundaries hold -1, below every defined statistic, so they never
  * block a peak; thr >= 0 takes part in the maximum before (t > thr and
- * t > max(before) is t > max(thr, before)).  The four windows on each side
- * share all but three of their W-1 values, so their maxima are built from
- * one common maximum.  With W = 0 the window is w_rt (at run time). */
-template <int W>
-__device__ __forceinline__ uint32_t ed_peaks4(const float *ts, int q0, int w_rt, float thr) {
+ * t > max(before) is t > max(thr, before)). */
+__device__ __forceinline__ uint32_t ed_peaks4(const float *ts, int q0, int w, float thr) {
   uint32_t bits = 0;
-  if constexpr (W > 0) {
-    constexpr int H = W - 1;          /* neighbours on each side, >= 1 */
-    constexpr int R = (H + 3) / 4;    /* float4s of neighbours on each side */
-    constexpr int NV = 4 + 8 * R;
-    constexpr int C = 4 * R;          /* v[C + j] is ts[q0 + j] */
-    float v[NV];
-    const float4 *p = reinterpret_cast<const float4 *>(ts + q0 - C);
 #pragma unroll
-    for (int f = 0; f < NV / 4; ++f) {
-      const float4 x = p[f];
-      v[4 * f] = x.x;
-      v[4 * f + 1] = x.y;
-      v[4 * f + 2] = x.z;
-      v[4 * f + 3] = x.w;
+  for (int j = 0; j < 4; ++j) {
+    const int q = q0 + j;
+    const float t = ts[q];
+    float lm = thr, rm = -1.0f;
+    for (int m = 1; m < w; ++m) {
+      lm = fmaxf(lm, ts[q - m]);
+      rm = fmaxf(rm, ts[q + m]);
     }
-    float L[4], Rm[4];
-    if constexpr (H >= 4) {
-      /* before: window j is v[C+j-H .. C+j-1]; all four hold v[C+3-H .. C-1] */
-      const float cl = run_max<C + 3 - H, H - 3>(v, thr);
-      const float a12 = max2(v[C - H + 1], v[C - H + 2]);
-      const float b01 = max2(v[C], v[C + 1]);
-      L[0] = max3(v[C - H], a12, cl);
-      L[1] = max3(a12, cl, v[C]);
-      L[2] = max3(v[C - H + 2], cl, b01);
-      L[3] = max3(cl, b01, v[C + 2]);
-      /* after: window j is v[C+j+1 .. C+j+H]; all four hold v[C+4 .. C+H] */
-      const float cr = run_max<C + 5, H - 4>(v, v[C + 4]);
-      const float c23 = max2(v[C + 2], v[C + 3]);
-      const float e12 = max2(v[C + H + 1], v[C + H + 2]);
-      Rm[0] = max3(v[C + 1], c23, cr);
-      Rm[1] = max3(c23, cr, v[C + H + 1]);
-      Rm[2] = max3(v[C + 3], cr, e12);
-      Rm[3] = max3(cr, e12, v[C + H + 3]);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        L[j] = thr;
-        Rm[j] = v[C + j + 1];
-#pragma unroll
-        for (int m = 1; m <= H; ++m) L[j] = max2(L[j], v[C + j - m]);
-#pragma unroll
-        for (int m = 2; m <= H; ++m) Rm[j] = max2(Rm[j], v[C + j + m]);
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) bits |= ((v[C + j] > L[j]) & (v[C + j] >= Rm[j])) ? (1u << j) : 0u;
-  } else {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int q = q0 + j;
-      const float t = ts[q];
-      float lm = thr, rm = -1.0f;
-      for (int m = 1; m < w_rt; ++m) {
-        lm = fmaxf(lm, ts[q - m]);
-        rm = fmaxf(rm, ts[q + m]);
-      }
-      bits |= ((t > lm) & (t >= rm)) ? (1u << j) : 0u;
-    }
+    bits |= ((t > lm) & (t >= rm)) ? (1u << j) : 0u;
   }
   return bits;
 }
@@ -330,10 +267,348 @@ __global__ void k_ed_tiles(DetectArgs a) {
   }
 }
 
-/* WS, WL: the detector windows fixed at compile time, or 0 to read them
- * from the arguments */
-template <int WS, int WL>
-__global__ __launch_bounds__(THREADS) void k_ed_detect(DetectArgs a) {
+/* ------------------------------------- change points, windows of 3 and 8 */
+
+/* The default windows, known at compile time: a wavefront takes a tile, a lane
+ * 16 consecutive boundaries of it.
+ *
+ * What bounds it: the vector instructions of the two statistics (about 1200 per
+ * lane for 16 boundaries); the samples are read once and a tile's results are
+ * 128 bytes.  Two wavefronts of a SIMD start simple float instructions side by
+ * side, but double-precision operations, of which a thread that takes the
+ * statistics from prefix sums in LDS runs 6 each, and 24-bit multiplications only
+ * alone: 291 M samples (4000 reads of 5 kb) take 966 us in that form, 625 in
+ * exact 32-bit integers and 513 in this.  A lane keeps
+ * its 16 + 2 * 8 samples as float32 in registers, and its window sums slide.  D and
+ * V are differences, the same integers for samples less a constant: with a constant
+ * near the lane's mean the sum of any 24 squares lies below 2^21 in any usual
+ * signal (a deviation of 295 all along), and then every sum, square and V is an
+ * integer below 2^24 (w (Q_l + Q_r) <= 8 * 2^21, and S_l^2 + S_r^2 is no larger),
+ * exact at each step.  A tile in which some lane's sum is larger takes
+ * wide_stats.  The roundings of the statistic's operands and its quotient are as
+ * in ed_stat. */
+constexpr int BPL = 16;          /* boundaries per lane */
+constexpr int HB = 8;            /* boundaries (and samples) looked at beyond a lane's or the tile's */
+constexpr int ROW = (64 + 2) * (BPL + 4); /* floats: lane l's statistics at (l+1) * 20, 16-byte pieces of 16 lanes in different banks */
+constexpr float MAX_SQUARES = 2097152.0f; /* of the 16 samples around a boundary, below which all is exact */
+static_assert(TS == 64 * BPL, "a wavefront per tile");
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+
+/* A tile's read as seen from the tile's first boundary: samples at x[lo .. hi],
+ * boundaries of a window w defined in [w - first, last - w] (32 bits, cut off
+ * beyond the tile's reach). */
+struct TileView {
+  const int16_t *x;
+  int lo, hi;
+  int odd;     /* 1: x lies two bytes after a multiple of four */
+  bool inside; /* every sample within 2 * HB + 2 of the tile is the read's */
+};
+
+__device__ __forceinline__ TileView tile_view(const int16_t *x, int64_t i0, int64_t n) {
+  TileView v;
+  v.x = x + i0;
+  v.lo = i0 < 64 ? -(int)i0 : -64;
+  v.hi = n - 1 - i0 < 4096 ? (int)(n - 1 - i0) : 4096;
+  v.odd = (int)(reinterpret_cast<uintptr_t>(v.x) >> 1) & 1;
+  v.inside = v.lo <= -2 * HB - 2 && v.hi >= TS + 2 * HB + 1;
+  return v;
+}
+
+__device__ __forceinline__ int sample_at(const TileView &v, int rel) {
+  return v.x[min(max(rel, v.lo), v.hi)];
+}
+
+/* samples rel .. rel + 2*NW - 1 (rel even) as pairs (outside the read: its
+ * nearest sample; no defined boundary reaches one).  A read's samples start at
+ * any even address: its words are read from multiples of four bytes. */
+template <int NW>
+__device__ __forceinline__ void sample_pairs(const TileView &v, int rel, uint32_t (&d)[NW]) {
+  if (v.inside) {
+    const u32x4_a4 *p = reinterpret_cast<const u32x4_a4 *>(v.x + rel - v.odd);
+#pragma unroll
+    for (int i = 0; i < NW / 4; ++i) {
+      const u32x4 q = p[i];
+      d[4 * i] = q.x;
+      d[4 * i + 1] = q.y;
+      d[4 * i + 2] = q.z;
+      d[4 * i + 3] = q.w;
+    }
+    if (v.odd) {
+      const uint32_t e = reinterpret_cast<const uint32_t *>(p)[NW];
+#pragma unroll
+      for (int i = 0; i < NW; ++i) d[i] = __builtin_amdgcn_alignbit(i + 1 < NW ? d[i + 1] : e, d[i], 16);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < NW; ++i)
+      d[i] = ((uint32_t)sample_at(v, rel + 2 * i) & 0xffffu) | ((uint32_t)sample_at(v, rel + 2 * i + 1) << 16);
+  }
+}
+
+/* a constant in a vector register: an instruction with a scalar or literal
+ * operand takes the place of two with vector operands */
+template <typename T>
+__device__ __forceinline__ T vreg(T c) {
+  T r;
+  asm("v_mov_b32 %0, %1" : "=v"(r) : "i"(c));
+  return r;
+}
+struct Consts {
+  uint32_t low, mag;
+  float tiny;
+};
+__device__ __forceinline__ Consts consts() {
+  return {vreg(0xffffu), vreg(0x4b008000u), __uint_as_float(vreg(0x1f800000u) /* 2^-64 */)};
+}
+
+/* 2*NW samples (pairs) less an integer near their mean, as floats: a sample plus
+ * 2^15 is put into the mantissa of 2^23, and differences of such floats are
+ * exact. */
+template <int NW>
+__device__ __forceinline__ void centred(const Consts &k, const uint32_t (&d)[NW], float (&y)[2 * NW]) {
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    y[2 * i] = __uint_as_float(__builtin_amdgcn_bitop3_b32(d[i], k.low, k.mag, 0x6a)); /* (d & low) ^ mag */
+    uint32_t high; /* (the compiler would take the half in the xor, an SDWA instruction, which starts alone) */
+    asm("v_lshrrev_b32 %0, 16, %1" : "=v"(high) : "v"(d[i]));
+    y[2 * i + 1] = __uint_as_float(high ^ k.mag);
+  }
+  /* four floats of [2^23, 2^24): their sum is a multiple of 4 */
+  const float c = ((y[NW / 4] + y[3 * NW / 4]) + (y[5 * NW / 4] + y[7 * NW / 4])) * 0.25f;
+#pragma unroll
+  for (int i = 0; i < 2 * NW; ++i) y[i] -= c;
+}
+
+/* The statistic of a window w from D and V (both exact), kept between the
+ * threshold and T_INF.  It stands for infinity: where V = 0 (V + 2^-64 is V
+ * otherwise) the quotient num / 2^-64 (num is 0 or 4 to 2^41) is 0 or beyond it,
+ * and no other statistic reaches 2^42.  Peaks depend on the order of statistics
+ * alone, and on that of none below the threshold. */
+constexpr float T_INF = 0x1p60f;
+__device__ __forceinline__ float kept_stat(const Consts &k, float w, float df, float v, float thr) {
+  const float num = (df * df) * w;
+  return __builtin_amdgcn_fmed3f(div_small(num, v + k.tiny), thr, T_INF);
+}
+
+/* the same from the window sums and the sum of squares over both windows */
+__device__ __forceinline__ float stat_f32(const Consts &k, float w, float sl, float sr, float q, float thr) {
+  return kept_stat(k, w, sr - sl, __builtin_fmaf(-sl, sl, __builtin_fmaf(-sr, sr, w * q)), thr);
+}
+
+/* The kept statistics of window W at N consecutive boundaries, the first with HB
+ * samples (pairs) before it, from any samples: sums in 32 bits, squares and V in
+ * double, all exact. */
+template <int W, int N, int NW>
+__device__ __forceinline__ void wide_stats(const Consts &ks, const uint32_t (&d)[NW], float thr, float (&t)[N]) {
+  static_assert(2 * NW >= N - 1 + 2 * HB, "samples on either side of each boundary");
+  auto x = [&](int k) { return (k & 1) ? (int)d[k / 2] >> 16 : (int)(int16_t)d[k / 2]; };
+  int sl = 0, sr = 0;
+  double q2 = 0.0;
+#pragma unroll
+  for (int k = HB - W; k < HB; ++k) {
+    sl += x(k);
+    sr += x(k + W);
+    q2 += (double)(x(k) * x(k)) + (double)(x(k + W) * x(k + W));
+  }
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    const double l = (double)sl, r = (double)sr;
+    const double v = __builtin_fma(-l, l, __builtin_fma(-r, r, (double)W * q2));
+    t[q] = kept_stat(ks, (float)W, (float)(sr - sl), (float)v, thr);
+    if (q + 1 < N) {
+      const int a = x(q + HB - W), b = x(q + HB), c = x(q + HB + W);
+      sl += b - a;
+      sr += c - b;
+      q2 += (double)(c * c) - (double)(a * a);
+    }
+  }
+}
+
+/* The peaks of window W (see ed_peaks4) at the lane's boundaries, one bit each,
+ * from the row of statistics, none below the threshold (raising a statistic
+ * to it changes no peak).  Windows of neighbours share their maxima. */
+template <int W>
+__device__ __forceinline__ uint32_t row_peaks(const float *row) {
+  constexpr int H = W - 1;
+  const int lane = threadIdx.x & 63;
+  float e[HB + BPL + HB]; /* boundaries -HB .. BPL + HB - 1 of the lane */
+  const float *own = row + (lane + 1) * (BPL + 4);
+#pragma unroll
+  for (int f = 0; f < (HB + BPL + HB) / 4; ++f) {
+    const int k = 4 * f - HB;
+    const float *p = k < 0 ? own - (BPL + 4) + BPL + k : k < BPL ? own + k : own + (BPL + 4) + k - BPL;
+    const float4 t = *reinterpret_cast<const float4 *>(p);
+    e[4 * f] = t.x;
+    e[4 * f + 1] = t.y;
+    e[4 * f + 2] = t.z;
+    e[4 * f + 3] = t.w;
+  }
+  float m[HB + BPL + HB]; /* m[i]: the largest of e[i .. i+H-1] */
+  if constexpr (H == 2) {
+#pragma unroll
+    for (int i = HB - H; i <= HB + BPL; ++i) m[i] = max2(e[i], e[i + 1]);
+  } else {
+    static_assert(H == 7, "windows of 3 and 8");
+    float m3[HB + BPL + HB];
+#pragma unroll
+    for (int i = HB - H; i <= HB + BPL + H - 3; ++i) m3[i] = max3(e[i], e[i + 1], e[i + 2]);
+#pragma unroll
+    for (int i = HB - H; i <= HB + BPL; ++i) m[i] = max3(m3[i], m3[i + 3], e[i + 6]);
+  }
+  uint32_t bits = 0;
+#pragma unroll
+  for (int q = 0; q < BPL; ++q)
+    bits |= ((e[HB + q] > m[HB + q - H]) & (e[HB + q] >= m[HB + q + 1])) ? (1u << q) : 0u;
+  return bits;
+}
+
+__device__ __forceinline__ void put_row(float *row, const float (&t)[BPL], float *halo, float h) {
+  float4 *own = reinterpret_cast<float4 *>(row + ((threadIdx.x & 63) + 1) * (BPL + 4));
+#pragma unroll
+  for (int f = 0; f < BPL / 4; ++f) own[f] = make_float4(t[4 * f], t[4 * f + 1], t[4 * f + 2], t[4 * f + 3]);
+  if ((threadIdx.x & 63) < 2 * HB) *halo = h;
+}
+
+__global__ __launch_bounds__(THREADS, 4) void k_ed_detect(DetectArgs a) {
+  constexpr int WS = 3, WL = 8;
+  /* thresholds as kept_stat orders them: above every finite statistic, but below
+   * infinity unless infinite themselves */
+  const float thr_s = a.thr_short == INFINITY ? T_INF : fminf(a.thr_short, 0.5f * T_INF);
+  const float thr_l = a.thr_long == INFINITY ? T_INF : fminf(a.thr_long, 0.5f * T_INF);
+  __shared__ __align__(16) float rows[THREADS / 64][ROW];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t g = blockIdx.x * (THREADS / 64) + wave;
+  if (g >= a.n_tiles) return;
+  float *row = rows[wave];
+  const EdTile tl = a.tiles[g];
+  const int64_t n = tl.n, i0 = tl.i0;
+  const TileView tv = tile_view(a.raw + tl.s0, i0, n);
+  /* the halo boundary of lanes 0 to 15 (HB before the tile, HB after it), and its place in the row */
+  const int hq = lane & (2 * HB - 1);
+  const int halo_rel = hq < HB ? hq - HB : TS + hq - HB;
+  float *halo = row + (hq < HB ? BPL - HB + hq : 65 * (BPL + 4) + hq - HB);
+
+  uint32_t d[BPL], h[HB]; /* samples around the lane's boundaries, and around its halo boundary */
+  sample_pairs(tv, BPL * lane - HB, d);
+  sample_pairs(tv, halo_rel - HB, h);
+  /* the first and last defined boundary of the two windows */
+  const int last = n - i0 < 8192 ? (int)(n - i0) : 8192;
+  const int first = i0 < 64 ? (int)i0 : 64;
+  /* boundary rel of window w is defined */
+  auto defined = [&](int rel, int w) { return rel >= w - first && rel <= last - w; };
+
+  float y[2 * BPL], u[2 * HB];
+  const Consts ks = consts();
+  centred(ks, d, y);
+  centred(ks, h, u);
+  const float w8 = __uint_as_float(vreg(0x41000000u)), w3 = __uint_as_float(vreg(0x40400000u));
+  float t[BPL], th;
+  bool ok;
+  { /* the long window: y[q .. q+7] and y[q+8 .. q+15] around boundary q */
+    float df[2 * BPL - WL], sl = 0.0f, sr = 0.0f, q2 = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 2 * BPL - WL; ++k) df[k] = y[k + WL] - y[k];
+#pragma unroll
+    for (int k = 0; k < WL; ++k) {
+      sl += y[k];
+      sr += y[k + WL];
+    }
+#pragma unroll
+    for (int k = 0; k < 2 * WL; ++k) q2 = __builtin_fmaf(y[k], y[k], q2);
+    const float q0 = q2;
+    float q8 = 0.0f;
+#pragma unroll
+    for (int q = 0; q < BPL; ++q) {
+      if (q == BPL / 2) q8 = q2;
+      t[q] = stat_f32(ks, w8, sl, sr, q2, thr_l);
+      sl += df[q];
+      if (q + WL < 2 * BPL - WL) sr += df[q + WL];
+      q2 = __builtin_fmaf(y[q + 2 * WL], y[q + 2 * WL], __builtin_fmaf(-y[q], y[q], q2));
+    }
+    /* the 16 squares around a boundary are among those of two of these sums */
+    ok = (q0 + q8 < MAX_SQUARES) & (q8 + q2 < MAX_SQUARES);
+    sl = sr = q2 = 0.0f;
+#pragma unroll
+    for (int k = 0; k < HB; ++k) {
+      sl += u[k];
+      sr += u[k + HB];
+      q2 = __builtin_fmaf(u[k + HB], u[k + HB], __builtin_fmaf(u[k], u[k], q2));
+    }
+    ok &= q2 < MAX_SQUARES;
+    th = stat_f32(ks, w8, sl, sr, q2, thr_l);
+  }
+  /* the long window's sums hold the short one's samples */
+  const bool wide = __ballot(!ok) != 0;
+  if (wide) {
+    float w[1];
+    sample_pairs(tv, BPL * lane - HB, d);
+    sample_pairs(tv, halo_rel - HB, h);
+    wide_stats<WL>(ks, d, thr_l, t);
+    wide_stats<WL>(ks, h, thr_l, w);
+    th = w[0];
+  }
+  if (!tv.inside) {
+#pragma unroll
+    for (int q = 0; q < BPL; ++q) t[q] = defined(BPL * lane + q, WL) ? t[q] : thr_l;
+    th = defined(halo_rel, WL) ? th : thr_l;
+  }
+  put_row(row, t, halo, th);
+  __builtin_amdgcn_sched_barrier(0); /* the two windows' registers are not needed at once */
+  { /* the short window */
+    float s3[BPL + WS], q2 = 0.0f; /* s3[k]: the sum of the window that ends before boundary k */
+#pragma unroll
+    for (int k = 0; k < BPL + WS; ++k) s3[k] = (y[k + HB - 3] + y[k + HB - 2]) + y[k + HB - 1];
+#pragma unroll
+    for (int k = HB - WS; k < HB + WS; ++k) q2 = __builtin_fmaf(y[k], y[k], q2);
+#pragma unroll
+    for (int q = 0; q < BPL; ++q) {
+      t[q] = stat_f32(ks, w3, s3[q], s3[q + WS], q2, thr_s);
+      q2 = __builtin_fmaf(y[q + HB + WS], y[q + HB + WS], __builtin_fmaf(-y[q + HB - WS], y[q + HB - WS], q2));
+    }
+    q2 = 0.0f;
+#pragma unroll
+    for (int k = HB - WS; k < HB + WS; ++k) q2 = __builtin_fmaf(u[k], u[k], q2);
+    th = stat_f32(ks, w3, (u[HB - 3] + u[HB - 2]) + u[HB - 1], (u[HB] + u[HB + 1]) + u[HB + 2], q2, thr_s);
+  }
+  if (wide) {
+    float w[1];
+    sample_pairs(tv, BPL * lane - HB, d);
+    sample_pairs(tv, halo_rel - HB, h);
+    wide_stats<WS>(ks, d, thr_s, t);
+    wide_stats<WS>(ks, h, thr_s, w);
+    th = w[0];
+  }
+  if (!tv.inside) {
+#pragma unroll
+    for (int q = 0; q < BPL; ++q) t[q] = defined(BPL * lane + q, WS) ? t[q] : thr_s;
+    th = defined(halo_rel, WS) ? th : thr_s;
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  /* a wavefront's LDS accesses are in order: one row serves both windows */
+  uint32_t bits = row_peaks<WL>(row);
+  put_row(row, t, halo, th);
+  bits |= row_peaks<WS>(row);
+
+  reinterpret_cast<uint16_t *>(a.flags + (uint64_t)g * WORDS)[lane] = (uint16_t)bits;
+  const uint32_t count = (uint32_t)__builtin_amdgcn_readlane(wave_scan((int)__popc(bits)), 63);
+  const uint64_t any = __ballot(bits != 0);
+  int cp = -1;
+  if (any) {
+    const int l = __builtin_ctzll(any);
+    cp = (int)(uint32_t)i0 + BPL * l + __builtin_ctz((uint32_t)__builtin_amdgcn_readlane((int)bits, l));
+  }
+  if (lane == 0) {
+    a.count[g] = count + (i0 == 0 ? 1u : 0u); /* the read's first event starts at sample 0 */
+    a.first_cp[g] = cp;                         /* the tile's first change point in the read, -1 if it has none */
+  }
+}
+
+/* ------------------------------------------- change points, other windows */
+
+/* One workgroup per tile, windows at run time. */
+__global__ __launch_bounds__(THREADS) void k_ed_detect_any(DetectArgs a) {
   /* the prefix sums, then (once every thread holds its statistics in
    * registers) the two rows of statistics in the same bytes: a smaller LDS
    * footprint, more workgroups per CU */
@@ -354,8 +629,7 @@ __global__ __launch_bounds__(THREADS) void k_ed_detect(DetectArgs a) {
   const int64_t n = tl.n;
   const int64_t i0 = tl.i0;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int ws = WS > 0 ? WS : a.w_short;
-  const int wl = WL > 0 ? WL : a.w_long;
+  const int ws = a.w_short, wl = a.w_long;
 
   /* samples i0-XH .. i0+TS+XH-1 */
   stage_prefix<NX>(a.raw + tl.s0, i0 - XH, n, P, PQ, wsum, wsq);
@@ -388,7 +662,7 @@ __global__ __launch_bounds__(THREADS) void k_ed_detect(DetectArgs a) {
   /* thread t: boundaries 4t .. 4t+3 of the tile (statistics q0 .. q0+3);
    * the neighbours read lie in q0-16 .. q0+19, inside [0, NT) */
   const int q0 = 4 * (int)threadIdx.x + THL;
-  const uint32_t nib = ed_peaks4<WS>(tsh, q0, ws, a.thr_short) | ed_peaks4<WL>(tlg, q0, wl, a.thr_long);
+  const uint32_t nib = ed_peaks4(tsh, q0, ws, a.thr_short) | ed_peaks4(tlg, q0, wl, a.thr_long);
   /* flag word m of the wave (its boundaries 64m .. 64m+63) is lanes 16m ..
    * 16m+15, four bits each: its low half from the row's lanes 0-7, its high
    * half from lanes 8-15, gathered by three row rotations (lane 7 and lane
@@ -621,9 +895,9 @@ hipError_t launch_detect(const DetectArgs &a, hipStream_t st, hipEvent_t *tev) {
     /* the two streaming kernels take their start and end from their own
      * dispatch when timed */
     if (a.w_short == 3 && a.w_long == 8)
-      hipExtLaunchKernelGGL((k_ed_detect<3, 8>), dim3(a.n_tiles), dim3(THREADS), 0, st, e0, e1, 0, a);
+      hipExtLaunchKernelGGL(k_ed_detect, dim3((a.n_tiles + 3) / 4), dim3(THREADS), 0, st, e0, e1, 0, a);
     else
-      hipExtLaunchKernelGGL((k_ed_detect<0, 0>), dim3(a.n_tiles), dim3(THREADS), 0, st, e0, e1, 0, a);
+      hipExtLaunchKernelGGL(k_ed_detect_any, dim3(a.n_tiles), dim3(THREADS), 0, st, e0, e1, 0, a);
     hipLaunchKernelGGL(k_ed_scan, dim3(nb), dim3(THREADS), 0, st, a);
   } else if (tev) {
     (void)hipEventRecord(e0, st);
