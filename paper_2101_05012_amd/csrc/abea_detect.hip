@@ -29,15 +29,13 @@
  *                  event count and first change point (k_ed_detect_any, a
  *                  workgroup per tile, for windows other than 3 and 8);
  *   k_ed_scan      exclusive scan of the tile counts, per 1024 tiles, then
- *                  over the blocks (k_ed_scan_top);
- *   k_ed_events    one workgroup per tile: the tile's event starts in order,
+ *                  over the blocks (k_ed_scan_top); with one block, also
+ *                  k_ed_offsets' work;
+ *   k_ed_events    one wavefront per tile: the tile's event starts in order,
  *                  the end of its last event from the first change point of
- *                  the read's next tiles, and one thread per event for its
+ *                  the read's next tiles, and one lane per event for its
  *                  statistics;
  *   k_ed_offsets   each read's first event.
- * Both streaming kernels stage their samples as prefix sums with wavefront
- * scans by DPP (no LDS permutes), and the statistics share the prefix
- * sums' LDS once those are no longer read.
  */
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
@@ -60,8 +58,6 @@ constexpr int NT = TS + 2 * THL;
 constexpr int WORDS = TS / 64; /* flag words per tile */
 constexpr int THREADS = 256;
 constexpr int SCAN_TILES = 1024; /* tiles per block of the first scan level */
-constexpr int EXT = 256; /* samples staged after the tile for events that run past it */
-constexpr int NE = TS + EXT; /* samples the event kernel stages per tile */
 
 /* a / b rounded to nearest, for 0 <= a < 2^64 and 1 <= b < 2^64: a
  * reciprocal estimate refined by one Newton step, a first quotient, and two
@@ -70,7 +66,8 @@ constexpr int NE = TS + EXT; /* samples the event kernel stages per tile */
  * quotient or reciprocal would leave the normal range and patches zero,
  * infinite and NaN operands, none of which arises here (a = 0 gives +0). */
 __device__ __forceinline__ float div_small(float a, float b) {
-  const float y0 = __builtin_amdgcn_rcpf(b);
+  float y0; /* the reciprocal starts alone: raised priority, see k_ed_detect */
+  asm("s_setprio 1\n\tv_rcp_f32 %0, %1\n\ts_setprio 0\n\ts_nop 0" : "=v"(y0) : "v"(b));
   const float e = __builtin_fmaf(-b, y0, 1.0f);
   const float y = __builtin_fmaf(e, y0, y0);
   const float q0 = a * y;
@@ -138,6 +135,14 @@ __device__ __forceinline__ uint32_t ed_peaks4(const float *ts, int q0, int w, fl
   return bits;
 }
 
+/* between LDS writes and reads by other lanes of the same wavefront: its accesses
+ * execute in order, and the compiler keeps them in order */
+__device__ __forceinline__ void wave_exchange() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 /* v of lane l-n of the same row of 16 lanes, cyclically (DPP row_ror:n) */
 template <int N>
 __device__ __forceinline__ uint32_t row_ror(uint32_t v) {
@@ -199,6 +204,11 @@ __device__ __forceinline__ long long wave_scan(long long v) {
   v += dpp_l<0x142, 0xA>(v);
   v += dpp_l<0x143, 0xC>(v);
   return v;
+}
+
+__device__ __forceinline__ long long last_lane(long long v) {
+  return (long long)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), 63) << 32) |
+                     (uint32_t)__builtin_amdgcn_readlane((int)v, 63));
 }
 
 template <int NS, typename QT>
@@ -278,7 +288,9 @@ __global__ void k_ed_tiles(DetectArgs a) {
  * side, but double-precision operations, of which a thread that takes the
  * statistics from prefix sums in LDS runs 6 each, and 24-bit multiplications only
  * alone: 291 M samples (4000 reads of 5 kb) take 966 us in that form, 625 in
- * exact 32-bit integers and 513 in this.  A lane keeps
+ * exact 32-bit integers and 460 in this.  The reciprocals, which start alone too,
+ * run at raised priority, so that the wavefronts at one pass it first and the
+ * others find partners (513 us without).  A lane keeps
  * its 16 + 2 * 8 samples as float32 in registers, and its window sums slide.  D and
  * V are differences, the same integers for samples less a constant: with a constant
  * near the lane's mean the sum of any 24 squares lies below 2^21 in any usual
@@ -320,26 +332,33 @@ __device__ __forceinline__ int sample_at(const TileView &v, int rel) {
   return v.x[min(max(rel, v.lo), v.hi)];
 }
 
-/* samples rel .. rel + 2*NW - 1 (rel even) as pairs (outside the read: its
- * nearest sample; no defined boundary reaches one).  A read's samples start at
- * any even address: its words are read from multiples of four bytes. */
+/* samples rel .. rel + 2*NW - 1 (rel even) of the read as pairs.  A read's
+ * samples start at any even address: the words are read from multiples of four
+ * bytes, from a sample before rel to two after the last. */
+template <int NW>
+__device__ __forceinline__ void word_pairs(const TileView &v, int rel, uint32_t (&d)[NW]) {
+  const u32x4_a4 *p = reinterpret_cast<const u32x4_a4 *>(v.x + rel - v.odd);
+#pragma unroll
+  for (int i = 0; i < NW / 4; ++i) {
+    const u32x4 q = p[i];
+    d[4 * i] = q.x;
+    d[4 * i + 1] = q.y;
+    d[4 * i + 2] = q.z;
+    d[4 * i + 3] = q.w;
+  }
+  if (v.odd) {
+    const uint32_t e = reinterpret_cast<const uint32_t *>(p)[NW];
+#pragma unroll
+    for (int i = 0; i < NW; ++i) d[i] = __builtin_amdgcn_alignbit(i + 1 < NW ? d[i + 1] : e, d[i], 16);
+  }
+}
+
+/* the same near the read's ends (outside it: its nearest sample; no defined
+ * boundary reaches one) */
 template <int NW>
 __device__ __forceinline__ void sample_pairs(const TileView &v, int rel, uint32_t (&d)[NW]) {
   if (v.inside) {
-    const u32x4_a4 *p = reinterpret_cast<const u32x4_a4 *>(v.x + rel - v.odd);
-#pragma unroll
-    for (int i = 0; i < NW / 4; ++i) {
-      const u32x4 q = p[i];
-      d[4 * i] = q.x;
-      d[4 * i + 1] = q.y;
-      d[4 * i + 2] = q.z;
-      d[4 * i + 3] = q.w;
-    }
-    if (v.odd) {
-      const uint32_t e = reinterpret_cast<const uint32_t *>(p)[NW];
-#pragma unroll
-      for (int i = 0; i < NW; ++i) d[i] = __builtin_amdgcn_alignbit(i + 1 < NW ? d[i + 1] : e, d[i], 16);
-    }
+    word_pairs(v, rel, d);
   } else {
 #pragma unroll
     for (int i = 0; i < NW; ++i)
@@ -587,8 +606,11 @@ __global__ __launch_bounds__(THREADS, 4) void k_ed_detect(DetectArgs a) {
   }
   __builtin_amdgcn_sched_barrier(0);
   /* a wavefront's LDS accesses are in order: one row serves both windows */
+  wave_exchange();
   uint32_t bits = row_peaks<WL>(row);
+  wave_exchange();
   put_row(row, t, halo, th);
+  wave_exchange();
   bits |= row_peaks<WS>(row);
 
   reinterpret_cast<uint16_t *>(a.flags + (uint64_t)g * WORDS)[lane] = (uint16_t)bits;
@@ -731,6 +753,8 @@ __device__ __forceinline__ uint64_t block_exclusive_scan(uint64_t v, uint64_t *s
 __global__ __launch_bounds__(THREADS) void k_ed_scan(DetectArgs a) {
   __shared__ uint64_t sh[THREADS / 64];
   const uint64_t t0 = (uint64_t)blockIdx.x * SCAN_TILES + 4u * threadIdx.x;
+  /* (the plan lies in host memory: requested early) */
+  const uint32_t tf = gridDim.x == 1 && (int)threadIdx.x <= a.n_reads ? a.tile_first[threadIdx.x] : 0;
   uint32_t c[4];
   uint64_t s = 0;
   for (int q = 0; q < 4; ++q) {
@@ -743,7 +767,21 @@ __global__ __launch_bounds__(THREADS) void k_ed_scan(DetectArgs a) {
     if (t0 + q < a.n_tiles) a.base[t0 + q] = p;
     p += c[q];
   }
-  if (threadIdx.x == 0) a.block_sum[blockIdx.x] = total;
+  if (gridDim.x > 1) {
+    if (threadIdx.x == 0) a.block_sum[blockIdx.x] = total;
+    return;
+  }
+  /* a batch of one block: its sums are done, and the reads' offsets are made here
+   * (16 reads of 5 kb: 4 launches rather than 6, of 2 to 3 us each) */
+  if (threadIdx.x == 0) {
+    a.block_sum[0] = 0;
+    a.block_sum[1] = total;
+  }
+  __syncthreads();
+  for (int r = threadIdx.x; r <= a.n_reads; r += THREADS) {
+    const uint32_t t = r == (int)threadIdx.x ? tf : a.tile_first[r];
+    a.event_offset[r] = t < a.n_tiles ? a.base[t] : total;
+  }
 }
 
 /* second level, one workgroup: exclusive scan of the block sums in place;
@@ -762,100 +800,166 @@ __global__ __launch_bounds__(THREADS) void k_ed_scan_top(DetectArgs a, uint32_t 
   if (threadIdx.x == 0) a.block_sum[n_blocks] = carry;
 }
 
-__global__ __launch_bounds__(THREADS) void k_ed_events(DetectArgs a) {
-  __shared__ uint64_t wf[WORDS];
-  __shared__ uint32_t wpre[WORDS + 1];
-  __shared__ int32_t starts[TS + 1];
-  __shared__ long long tail_end;
-  /* prefix sums of samples i0 .. i0+TS+EXT-1 of the read (zero past its end) */
-  __shared__ int P[NE + 1];
-  __shared__ long long PQ[NE + 1];
-  __shared__ int wsum[THREADS / 64];
-  __shared__ long long wsq[THREADS / 64];
-  const uint32_t g = blockIdx.x;
-  const EdTile tl = a.tiles[g];
-  const int r = (int)tl.read;
-  const int64_t n = tl.n;
-  const int64_t i0 = tl.i0;
-  const int first = (i0 == 0) ? 1 : 0;
-  const uint64_t gbase = a.base[g] + a.block_sum[g / SCAN_TILES];
-  const int16_t *x = a.raw + tl.s0;
+namespace {
 
-  if (threadIdx.x < WORDS) wf[threadIdx.x] = a.flags[(uint64_t)g * WORDS + threadIdx.x];
-  if (threadIdx.x == 0) tail_end = n;
-  stage_prefix<NE>(x, i0, n, P, PQ, wsum, wsq);
-  /* the event that runs past the tile ends at the read's next change point:
-   * the first change point of the first later tile of the read that has one
-   * (first_cp grows with the tile), or at the read's end; 256 tiles a step */
-  for (uint32_t h0 = g + 1; h0 < tl.g_end; h0 += THREADS) {
-    const uint32_t h = h0 + threadIdx.x;
-    const int32_t f = h < tl.g_end ? a.first_cp[h] : -1;
-    if (f >= 0) atomicMin(&tail_end, (long long)f);
-    if (__syncthreads_or(f >= 0)) break;
-  }
-  /* the events before each flag word (wf is visible: stage_prefix ends with
-   * a barrier): a scan of the 16 words' counts over 16 lanes of the first
-   * wavefront */
-  static_assert(WORDS == 16, "one lane per flag word");
-  if (threadIdx.x < WORDS) {
-    const uint32_t c = (uint32_t)__popcll(wf[threadIdx.x]);
-    uint32_t inc = c;
+/* a / b and the square root in double, rounded to nearest, for the operands that
+ * arise here (without the general forms' care for tiny, huge and special ones).
+ *
+ * b: a whole number below 2^16, r its reciprocal to within an ulp or two.  The
+ * residual a - q b is exact, and so is its share of the quotient to 2^-50 ulp,
+ * while a / b lies at least 2^-17 ulp from the middle of two doubles, or on a
+ * double. */
+__device__ __forceinline__ double small_rcp(double b) {
+  double r = __builtin_amdgcn_rcp(b); /* about 2^-23 */
+  r = __builtin_fma(__builtin_fma(-b, r, 1.0), r, r);
+  return __builtin_fma(__builtin_fma(-b, r, 1.0), r, r);
+}
+__device__ __forceinline__ double small_div(double a, double b, double r) {
+  const double q = a * r;
+  return __builtin_fma(__builtin_fma(-q, b, a), r, q);
+}
+/* v: 0, or a whole number below 2^64; Newton's iteration for v^-1/2, coupled with
+ * that for v^1/2, and two corrections from the residual */
+__device__ __forceinline__ double whole_sqrt(double v) {
+  const double x = v == 0.0 ? 1.0 : v;
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double e = __builtin_fma(-h, g, 0.5);
+  g = __builtin_fma(g, e, g);
+  h = __builtin_fma(h, e, h);
+  g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+  g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+  return v == 0.0 ? 0.0 : g;
+}
+
+}  // namespace
+
+/* Events of a tile, a wavefront per tile, a lane 16 consecutive samples of it.
+ *
+ * What bounds it: the instructions per event (double precision) and per sample,
+ * with the stores (12 B per event) behind them.  A workgroup per tile that stages
+ * prefix sums of all samples in LDS, between barriers, and takes each event's two
+ * divisions and root in their general forms needs 1050 us for 4000 reads of 5 kb
+ * (284908 tiles); this form 334 us, 3.6 TB/s of samples and events.  Here a lane's prefix sums stay in registers, one wavefront
+ * scan joins them, and only those at the tile's event starts go to LDS, in order,
+ * for the lanes that take an event each; a wavefront waits for no other.
+ *
+ * MAXE: the most events that can start in a tile (peaks of a window w lie w or
+ * more apart, so at most ceil(TS / w) of each detector, and the read's start). */
+template <int MAXE, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_ed_events(DetectArgs a) {
+  __shared__ uint4 lists[WAVES][MAXE + 1]; /* event starts: position, sums of x and x^2 before it */
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t g = blockIdx.x * WAVES + wave;
+  if (g >= a.n_tiles) return;
+  uint4 *list = lists[wave];
+  const EdTile tl = a.tiles[g];
+  const int64_t i0 = tl.i0;
+  const int left = (int)((int64_t)tl.n - i0); /* samples from the tile's first to the read's end */
+  const TileView tv = tile_view(a.raw + tl.s0, i0, tl.n);
+
+  /* loads first: the first change points of the read's next 64 tiles, the flags
+   * of the lane's boundaries, its samples, and 64 after the tile */
+  const int f = (int64_t)g + 1 + lane < (int64_t)tl.g_end ? a.first_cp[g + 1 + lane] : -1;
+  uint32_t bits = reinterpret_cast<const uint16_t *>(a.flags + (uint64_t)g * WORDS)[lane];
+  int x[BPL];
+  if (tv.hi > TS && (tv.lo < 0 || !tv.odd)) {
+    uint32_t d[BPL / 2];
+    word_pairs(tv, BPL * lane, d);
 #pragma unroll
-    for (int d = 1; d < WORDS; d <<= 1) {
-      const uint32_t o = __shfl_up(inc, d, WORDS);
-      if ((int)threadIdx.x >= d) inc += o;
-    }
-    wpre[threadIdx.x] = (uint32_t)first + inc - c;
-    if (threadIdx.x == WORDS - 1) wpre[WORDS] = (uint32_t)first + inc;
-    if (threadIdx.x == 0 && first) starts[0] = 0;
+    for (int k = 0; k < BPL; ++k) x[k] = (k & 1) ? (int)d[k / 2] >> 16 : (int)(int16_t)d[k / 2];
+  } else {
+#pragma unroll
+    for (int k = 0; k < BPL; ++k) x[k] = BPL * lane + k < left ? sample_at(tv, BPL * lane + k) : 0;
   }
-  __syncthreads();
-  /* a wavefront holds one flag word (k & 63 is the lane): a set bit's rank
-   * in it is the count of set bits of the lanes below (mbcnt) */
-  for (int k = threadIdx.x; k < TS; k += THREADS) {
-    const uint64_t m = wf[k >> 6];
-    if ((m >> (k & 63)) & 1u) {
-      const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-      starts[wpre[k >> 6] + below] = (int32_t)(i0 + k);
+  const int xt = TS + lane < left ? sample_at(tv, TS + lane) : 0;
+  const uint64_t gbase = a.base[g] + a.block_sum[g / SCAN_TILES];
+
+  /* the event that runs past the tile ends at the read's next change point: the
+   * first change point of the first later tile that has one, or the read's end */
+  int64_t end = left;
+  uint64_t has = __ballot(f >= 0);
+  if (has) {
+    end = (int64_t)__builtin_amdgcn_readlane(f, __builtin_ctzll(has)) - i0;
+  } else {
+    for (int64_t h0 = (int64_t)g + 65; h0 < (int64_t)tl.g_end; h0 += 64) {
+      const int fh = h0 + lane < (int64_t)tl.g_end ? a.first_cp[h0 + lane] : -1;
+      has = __ballot(fh >= 0);
+      if (has) {
+        end = (int64_t)__builtin_amdgcn_readlane(fh, __builtin_ctzll(has)) - i0;
+        break;
+      }
     }
   }
-  __syncthreads();
-  const int n_ev = (int)wpre[WORDS];
-  const double off = (double)a.offset[r];
-  const double sc = (double)a.pa_scale[r];
-  const int64_t lim = i0 + NE; /* staged: [i0, lim) */
-  for (int e = threadIdx.x; e < n_ev; e += THREADS) {
-    const uint64_t idx = gbase + (uint64_t)e;
-    if (idx >= a.capacity) continue;
-    const int64_t b0 = starts[e];
-    const int64_t b1 = (e + 1 < n_ev) ? (int64_t)starts[e + 1] : (int64_t)tail_end;
-    /* the event's sums from the staged prefix sums; past the staged range
-     * (an event that runs far beyond the tile) from memory */
-    const int64_t bs = b1 < lim ? b1 : lim;
-    int64_t s = (int64_t)P[bs - i0] - P[b0 - i0];
-    int64_t q = PQ[bs - i0] - PQ[b0 - i0];
-    for (int64_t j = bs; j < b1; ++j) {
-      const int64_t v = x[j];
+  /* the sums of the samples past the tile up to there */
+  int64_t ts, tq;
+  if (end <= TS + 64) {
+    const int v = TS + lane < end ? xt : 0;
+    ts = __builtin_amdgcn_readlane(wave_scan(v), 63);
+    tq = last_lane(wave_scan((long long)(v * v)));
+  } else {
+    long long s = xt, q = xt * xt;
+    for (int64_t k = TS + 64 + lane; k < end; k += 64) {
+      const int v = tv.x[k];
       s += v;
       q += v * v;
     }
-    const int64_t len = b1 - b0;
-    /* an event is no longer than its read (< 2^31 samples): its length
-     * converts from 32 bits, to the same value */
-    const int32_t len32 = (int32_t)len;
-    const double dlen = (double)len32;
+    ts = last_lane(wave_scan(s));
+    tq = last_lane(wave_scan(q));
+  }
+
+  /* sums before each sample of the lane, then before the lane */
+  int sp[BPL], s = 0;
+  long long qp[BPL], q = 0;
+#pragma unroll
+  for (int k = 0; k < BPL; ++k) {
+    sp[k] = s;
+    qp[k] = q;
+    s += x[k];
+    q += x[k] * x[k];
+  }
+  const int si = wave_scan(s);
+  const long long qi = wave_scan(q);
+  if (i0 == 0 && lane == 0) bits |= 1u; /* a read's first event starts at sample 0 */
+  const int ni = wave_scan((int)__popc(bits));
+  const int n_ev = __builtin_amdgcn_readlane(ni, 63);
+  uint4 *at = list + (ni - (int)__popc(bits));
+#pragma unroll
+  for (int k = 0; k < BPL; ++k) {
+    if ((bits >> k) & 1u) {
+      const long long qk = qi - q + qp[k];
+      *at++ = make_uint4((uint32_t)(BPL * lane + k), (uint32_t)(si - s + sp[k]), (uint32_t)qk, (uint32_t)(qk >> 32));
+    }
+  }
+  if (lane == 63) {
+    const long long qk = qi + tq;
+    list[n_ev] = make_uint4((uint32_t)end, (uint32_t)si + (uint32_t)ts, (uint32_t)qk, (uint32_t)((uint64_t)qk >> 32));
+  }
+  wave_exchange();
+
+  const double off = (double)a.offset[tl.read];
+  const double sc = (double)a.pa_scale[tl.read];
+  for (int e = lane; e < n_ev; e += 64) {
+    const uint64_t idx = gbase + (uint64_t)e;
+    const uint4 e0 = list[e], e1 = list[e + 1];
+    const int32_t len = (int32_t)(e1.x - e0.x);
+    const int32_t s32 = (int32_t)(e1.y - e0.y);
+    const int64_t qe = (int64_t)((((uint64_t)e1.w << 32) | e1.z) - (((uint64_t)e0.w << 32) | e0.z));
+    const double dlen = (double)len;
     /* len^2 times the population variance, exact, rounded once to double:
      * below 2^16 samples S fits 32 bits and len * Q and S^2 stay below 2^62
      * (samples are 16-bit), so 64 bits hold it; longer events take 128 */
-    double m, vd;
+    double m, sd;
     if (len < 65536) {
-      const int32_t s32 = (int32_t)s;
-      m = (double)s32 / dlen;
-      vd = (double)(uint64_t)((int64_t)len32 * q - (int64_t)s32 * s32);
-    } else {
-      m = (double)s / dlen;
-      const unsigned __int128 vv = (unsigned __int128)((__int128)len * q - (__int128)s * s);
+      const double r = small_rcp(dlen);
+      m = small_div((double)s32, dlen, r);
+      sd = small_div(whole_sqrt((double)(uint64_t)((int64_t)len * qe - (int64_t)s32 * s32)), dlen, r);
+    } else { /* the tile's last event: what of its sum lies in the tile, and past it */
+      const int64_t se = (int64_t)(int32_t)(e1.y - (uint32_t)ts - e0.y) + ts;
+      m = (double)se / dlen;
+      const unsigned __int128 vv = (unsigned __int128)((__int128)len * qe - (__int128)se * se);
       const uint64_t hi = (uint64_t)(vv >> 64);
+      double vd;
       if (hi == 0) {
         vd = (double)(uint64_t)vv;
       } else {
@@ -865,11 +969,13 @@ __global__ __launch_bounds__(THREADS) void k_ed_events(DetectArgs a) {
         const uint64_t top = (uint64_t)(vv >> k) | (low != 0 ? 1u : 0u);
         vd = __builtin_ldexp((double)top, k);
       }
+      sd = __builtin_sqrt(vd) / dlen;
     }
+    if (idx >= a.capacity) continue;
     float *ev = a.events + 3 * idx;
     ev[0] = (float)((m + off) * sc);
-    ev[1] = (float)(__builtin_sqrt(vd) / dlen * sc);
-    ev[2] = (float)len32;
+    ev[1] = (float)(sd * sc);
+    ev[2] = (float)len;
   }
 }
 
@@ -903,15 +1009,20 @@ hipError_t launch_detect(const DetectArgs &a, hipStream_t st, hipEvent_t *tev) {
     (void)hipEventRecord(e0, st);
     (void)hipEventRecord(e1, st);
   }
-  hipLaunchKernelGGL(k_ed_scan_top, dim3(1), dim3(THREADS), 0, st, a, nb);
+  if (nb != 1) hipLaunchKernelGGL(k_ed_scan_top, dim3(1), dim3(THREADS), 0, st, a, nb);
   if (a.n_tiles > 0) {
-    hipExtLaunchKernelGGL(k_ed_events, dim3(a.n_tiles), dim3(THREADS), 0, st, e2, e3, 0, a);
+    /* the event lists' room decides how many wavefronts a CU holds */
+    const int most = (TS + a.w_short - 1) / a.w_short + (TS + a.w_long - 1) / a.w_long + 1;
+    if (most <= 480)
+      hipExtLaunchKernelGGL((k_ed_events<480, 4>), dim3((a.n_tiles + 3) / 4), dim3(256), 0, st, e2, e3, 0, a);
+    else
+      hipExtLaunchKernelGGL((k_ed_events<TS + 1, 2>), dim3((a.n_tiles + 1) / 2), dim3(128), 0, st, e2, e3, 0, a);
   } else if (tev) {
     (void)hipEventRecord(e2, st);
     (void)hipEventRecord(e3, st);
   }
   const int nr = a.n_reads + 1;
-  hipLaunchKernelGGL(k_ed_offsets, dim3((nr + 255) / 256), dim3(256), 0, st, a, nb);
+  if (nb != 1) hipLaunchKernelGGL(k_ed_offsets, dim3((nr + 255) / 256), dim3(256), 0, st, a, nb);
   if (tev) {
     const hipError_t e = hipEventRecord(tev[5], st);
     if (e != hipSuccess) return e;
