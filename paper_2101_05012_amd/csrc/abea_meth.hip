@@ -25,7 +25,7 @@
  *                  in path order, so a k-mer's pairs are consecutive);
  *   k_meth_sites   one workgroup per 8192 k-mers of one read: the sites
  *                  appended to a list (one atomic per workgroup), NaN / 0
- *                  written for every k-mer that is not a scored site;
+ *                  written for every k-mer;
  *   k_meth_llr     one thread per listed site: both profiles in registers (a
  *                  column of at most ABEA_MAX_K cells per model), then the LLR.
  */
@@ -60,11 +60,20 @@ __global__ __launch_bounds__(256) void k_meth_stage(const uint64_t *src, uint64_
   if (i < words) dst[i] = src[i];
 }
 
-/* one workgroup per tile, a run of CHUNK pairs of one read (thread t takes
- * the run's pairs t, t+256, ...): the first and the last event paired with
- * each k-mer (a k-mer's pairs are consecutive in the path order).  The
- * read's fields are workgroup-uniform; the pairs are loaded eight
- * iterations ahead of the stores that use them. */
+/* v of the lane below (above), and `edge` in lane 0 (63): DPP wave_shr:1, wave_shl:1 */
+__device__ __forceinline__ int lane_below(int edge, int v) {
+  return __builtin_amdgcn_update_dpp(edge, v, 0x138, 0xF, 0xF, false);
+}
+__device__ __forceinline__ int lane_above(int edge, int v) {
+  return __builtin_amdgcn_update_dpp(edge, v, 0x130, 0xF, 0xF, false);
+}
+
+/* one workgroup per tile, a run of CHUNK pairs of one read, a quarter of it per
+ * wavefront: the first and the last event paired with each k-mer (a k-mer's
+ * pairs are consecutive in the path order).  The read's fields are
+ * workgroup-uniform; the wavefront loads G * 64 consecutive pairs, once, and
+ * takes a pair's neighbours from the lanes beside it (three loads per pair: 181
+ * us for 4000 reads of 5 kb, this 153). */
 __global__ __launch_bounds__(256) void k_meth_bounds(MethArgs a) {
   const MethTile tl = a.pair_tiles[blockIdx.x];
   const int r = (int)tl.read;
@@ -72,36 +81,43 @@ __global__ __launch_bounds__(256) void k_meth_bounds(MethArgs a) {
   const uint64_t p0 = a.pair_offset[r], p1 = a.pair_offset[r + 1];
   const uint64_t c0 = p0 + (uint64_t)tl.chunk * CHUNK;
   if (c0 >= p1) return;
-  const uint64_t c1 = c0 + CHUNK < p1 ? c0 + CHUNK : p1;
   const MethRead rd = a.reads[r];
-  constexpr int G = 8;
-  for (int g = 0; g < CHUNK / 256; g += G) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int G = 8, PER_WAVE = CHUNK / 4;
+  for (int g = 0; g < PER_WAVE; g += G * 64) {
+    const uint64_t pw = c0 + (uint64_t)(wave * PER_WAVE + g);
+    if (pw >= p1) return;
     int2 q[G];
-    int yp[G], yn[G];
 #pragma unroll
     for (int u = 0; u < G; ++u) {
-      const uint64_t p = c0 + (uint64_t)(g + u) * 256 + threadIdx.x;
-      q[u] = make_int2(0, -1);
-      yp[u] = yn[u] = INT32_MIN; /* no neighbour: the run of the k-mer ends here */
-      if (p < c1) {
-        q[u] = a.pairs[p];
-        if (p > p0) yp[u] = a.pairs[p - 1].y;
-        if (p + 1 < p1) yn[u] = a.pairs[p + 1].y;
-      }
+      const uint64_t p = pw + (uint64_t)(64 * u + lane);
+      q[u] = p < p1 ? a.pairs[p] : make_int2(0, -1);
     }
+    /* the k-mers before and after the run (none: no k-mer's) */
+    int edge = INT32_MIN;
+    if (lane == 0 && pw > p0) edge = a.pairs[pw - 1].y;
+    if (lane == 63 && pw + G * 64 < p1) edge = a.pairs[pw + G * 64].y;
 #pragma unroll
     for (int u = 0; u < G; ++u) {
-      if (q[u].y < 0 || q[u].y >= rd.n_k) continue;
-      if (yp[u] != q[u].y) a.kfirst[rd.km_off + q[u].y] = q[u].x;
-      if (yn[u] != q[u].y) a.klast[rd.km_off + q[u].y] = q[u].x;
+      const int y = q[u].y;
+      const int yp = lane_below(u == 0 ? edge : __builtin_amdgcn_readlane(q[u > 0 ? u - 1 : 0].y, 63), y);
+      const int yn = lane_above(u == G - 1 ? edge : __builtin_amdgcn_readlane(q[u < G - 1 ? u + 1 : u].y, 0), y);
+      if (y < 0 || y >= rd.n_k) continue;
+      if (yp != y) a.kfirst[rd.km_off + y] = q[u].x;
+      if (yn != y) a.klast[rd.km_off + y] = q[u].x;
     }
   }
 }
 
-/* one workgroup per tile, a run of CHUNK k-mers of one read: the sites of an
- * aligned read go to the list (one atomic per workgroup: the sites are found
- * and counted first, one bit per iteration kept by each thread, then written
- * at the workgroup's base), every other k-mer gets NaN and 0 */
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
+/* one workgroup per tile, a run of CHUNK k-mers of one read, four consecutive per
+ * thread and step: the sites of an aligned read go to the list (one atomic per
+ * workgroup: the sites are found and counted first, four bits per step kept by
+ * each thread, then written at the workgroup's base), and every k-mer gets NaN
+ * and 0, which k_meth_llr replaces at the sites (a k-mer per thread and step: 118
+ * us for 4000 reads of 5 kb, this 87) */
 __global__ __launch_bounds__(256) void k_meth_sites(MethArgs a) {
   __shared__ uint32_t wcount[4], wbase[4];
   const MethTile tl = a.kmer_tiles[blockIdx.x];
@@ -110,14 +126,34 @@ __global__ __launch_bounds__(256) void k_meth_sites(MethArgs a) {
   const MethRead rd = a.reads[r];
   const bool ok = a.status[r] == READ_OK;
   const uint32_t j0 = tl.chunk * (uint32_t)CHUNK; /* the run's first k-mer in the read */
-  const uint32_t j1 = (uint32_t)rd.n_k - j0 < (uint32_t)CHUNK ? (uint32_t)rd.n_k : j0 + CHUNK;
+  const uint32_t nj = (uint32_t)rd.n_k - j0 < (uint32_t)CHUNK ? (uint32_t)rd.n_k - j0 : (uint32_t)CHUNK;
+  constexpr int STEPS = CHUNK / 1024;
+  static_assert(STEPS * 4 == 32, "a thread's sites in one word");
+  const uint32_t *rank = a.ranks + rd.km_off + j0;
+  float *llr = a.llr + rd.km_off + j0;
+  int32_t *n_ev = a.n_ev ? a.n_ev + rd.km_off + j0 : nullptr;
   uint32_t bits = 0, cnt = 0;
-#pragma unroll 8
-  for (int it = 0; it < CHUNK / 256; ++it) {
-    const uint32_t j = j0 + (uint32_t)it * 256 + threadIdx.x;
-    const bool site = ok && j < j1 && is_site(a.ranks[rd.km_off + j], a.k);
-    bits |= (uint32_t)site << it;
-    cnt += (uint32_t)__popcll(__ballot(site));
+#pragma unroll
+  for (int it = 0; it < STEPS; ++it) {
+    const uint32_t j = (uint32_t)(it * 1024) + 4u * threadIdx.x;
+    uint32_t b = 0;
+    if (j + 4 <= nj) {
+      const u32x4_a4 k4 = *reinterpret_cast<const u32x4_a4 *>(rank + j);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) b |= (uint32_t)is_site(k4[u], a.k) << u;
+      *reinterpret_cast<f32x4_a4 *>(llr + j) = f32x4_a4{NAN, NAN, NAN, NAN};
+      if (n_ev) *reinterpret_cast<u32x4_a4 *>(n_ev + j) = u32x4_a4{0, 0, 0, 0};
+    } else {
+      for (uint32_t u = 0; u < 4 && j + u < nj; ++u) {
+        b |= (uint32_t)is_site(rank[j + u], a.k) << u;
+        llr[j + u] = NAN;
+        if (n_ev) n_ev[j + u] = 0;
+      }
+    }
+    if (!ok) b = 0;
+    bits |= b << (4 * it);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) cnt += (uint32_t)__popcll(__ballot((b >> u) & 1u));
   }
   if (lane == 0) wcount[wave] = cnt;
   __syncthreads();
@@ -132,92 +168,130 @@ __global__ __launch_bounds__(256) void k_meth_sites(MethArgs a) {
   }
   __syncthreads();
   uint32_t run = wbase[wave];
-  for (int it = 0; it < CHUNK / 256; ++it) {
-    const uint32_t j = j0 + (uint32_t)it * 256 + threadIdx.x;
-    const bool site = (bits >> it) & 1u;
-    const uint64_t m = __ballot(site);
-    if (site) {
-      const uint32_t slot = run + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-      a.sites[slot] = make_uint2((uint32_t)r, j);
-    } else if (j < j1) {
-      a.llr[rd.km_off + j] = NAN;
-      if (a.n_ev) a.n_ev[rd.km_off + j] = 0;
+#pragma unroll
+  for (int it = 0; it < STEPS; ++it) {
+    const uint32_t b = (bits >> (4 * it)) & 15u;
+    uint32_t slot = run;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint64_t m = __ballot((b >> u) & 1u);
+      slot += (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+      run += (uint32_t)__popcll(m);
     }
-    run += (uint32_t)__popcll(m);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if ((b >> u) & 1u) a.sites[slot++] = make_uint2((uint32_t)r, j0 + (uint32_t)(it * 1024 + u) + 4u * threadIdx.x);
   }
 }
 
-__global__ __launch_bounds__(256) void k_meth_llr(MethArgs a) {
+/* One thread per site: both profiles' columns in registers.
+ *
+ * What bounds it: the gathers of a site (its k-mers, their entries of two models,
+ * its events), each from a cache line of its own; most miss the L1, whose pending
+ * lines then hold the others up (411 us for the 2 M sites of 4000 reads of 5 kb).
+ * K, the longest window, is the context's k where that is 5, 6 or 9, and else
+ * KMAX: registers for the k alone, and AHEAD events requested at once (375 us).
+ * Up to k = 6 both models' tables (128 KB at most) lie in LDS, one workgroup of
+ * LLR_LDS_THREADS per CU: 301 us.  A window cut off by the read's start is filled
+ * up in front with k-mers whose emission is -inf. */
+constexpr int AHEAD = 4;
+constexpr int LLR_LDS_THREADS = 1024;
+template <int K>
+struct LlrModels {
+  static constexpr bool LDS = K <= 6;
+  static constexpr int ENTRIES = LDS ? 1 << (2 * K) : 1;
+  static constexpr int THREADS = LDS ? LLR_LDS_THREADS : 256;
+};
+static_assert(sizeof(ModelEntry) == sizeof(float4), "an entry is read as a float4");
+
+template <int K>
+__global__ __launch_bounds__(LlrModels<K>::THREADS) void k_meth_llr(MethArgs a) {
+  constexpr bool LDS = LlrModels<K>::LDS;
+  __shared__ float4 tab[LDS ? 2 : 1][LlrModels<K>::ENTRIES];
   const uint32_t n_sites = *a.n_sites;
+  if (LDS) {
+    if (blockIdx.x * blockDim.x >= n_sites) return;
+    for (int j = threadIdx.x; j < LlrModels<K>::ENTRIES; j += LlrModels<K>::THREADS) {
+      tab[0][j] = reinterpret_cast<const float4 *>(a.model)[j];
+      tab[LDS ? 1 : 0][j] = reinterpret_cast<const float4 *>(a.meth_model)[j];
+    }
+    __syncthreads();
+  }
   const float NI = -INFINITY;
+  const int k = K == KMAX ? a.k : K;
   for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < n_sites; s += gridDim.x * blockDim.x) {
     const uint2 st = a.sites[s];
     const MethRead rd = a.reads[st.x];
     const int32_t i = (int32_t)st.y;
-    const int32_t j0 = i - (a.k - 1) > 0 ? i - (a.k - 1) : 0;
-    const int32_t nk = i - j0 + 1;
+    const int32_t j0 = i - (k - 1) > 0 ? i - (k - 1) : 0;
+    const int first = K - (i - j0 + 1); /* the window's first k-mer among the K */
     const int32_t e0 = a.kfirst[rd.km_off + j0], e1 = a.klast[rd.km_off + i];
     const float scale = a.scale[st.x], shift = a.shift[st.x];
-    /* the window's k-mer parameters under both models */
-    float mu_u[KMAX], c_u[KMAX], h_u[KMAX], mu_m[KMAX], c_m[KMAX], h_m[KMAX];
-#pragma unroll
-    for (int j = 0; j < KMAX; ++j) {
-      if (j < nk) {
-        const uint32_t rk = a.ranks[rd.km_off + j0 + j];
-        const ModelEntry u = a.model[rk], m = a.meth_model[rk];
-        mu_u[j] = a.scale_events ? u.mean : __builtin_fmaf(u.mean, scale, shift);
-        mu_m[j] = a.scale_events ? m.mean : __builtin_fmaf(m.mean, scale, shift);
-        c_u[j] = u.c;
-        h_u[j] = u.h;
-        c_m[j] = m.c;
-        h_m[j] = m.h;
-      } else {
-        mu_u[j] = mu_m[j] = c_u[j] = c_m[j] = h_u[j] = h_m[j] = 0.0f;
-      }
-    }
-    /* columns of the previous event (up and diagonal neighbours) */
-    float su[KMAX], sm[KMAX];
-#pragma unroll
-    for (int j = 0; j < KMAX; ++j) su[j] = sm[j] = NI;
     const float *xm = a.events + (uint64_t)a.ev_stride * rd.ev_off;
-    /* the next event's mean is loaded while this one's row is computed */
-    float xnext = xm[(uint64_t)a.ev_stride * e0];
-    for (int32_t e = e0; e <= e1; ++e) {
-      float x = xnext;
-      if (e < e1) xnext = xm[(uint64_t)a.ev_stride * (e + 1)];
-      if (a.scale_events) {
-        const float d = x - shift;
-        x = d / scale;
-      }
-      float du = (e == e0) ? 0.0f : NI; /* diagonal of k-mer 0: the origin before the first cell */
-      float dm = du;
-      float lu = NI, lm = NI; /* left neighbours in this event's row */
+    float xn[AHEAD];
 #pragma unroll
-      for (int j = 0; j < KMAX; ++j) {
-        if (j < nk) {
+    for (int u = 0; u < AHEAD; ++u) xn[u] = xm[(uint64_t)a.ev_stride * (uint64_t)min(e0 + u, max(e0, e1))];
+    /* the window's k-mer parameters under both models */
+    float mu_u[K], c_u[K], h_u[K], mu_m[K], c_m[K], h_m[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      const uint32_t rk = a.ranks[rd.km_off + (uint64_t)(i - min(K - 1 - j, i - j0))];
+      float4 u, m; /* mean, c, h */
+      if (LDS) {
+        u = tab[0][rk & (uint32_t)(LlrModels<K>::ENTRIES - 1)];
+        m = tab[LDS ? 1 : 0][rk & (uint32_t)(LlrModels<K>::ENTRIES - 1)];
+      } else {
+        u = reinterpret_cast<const float4 *>(a.model)[rk];
+        m = reinterpret_cast<const float4 *>(a.meth_model)[rk];
+      }
+      mu_u[j] = a.scale_events ? u.x : __builtin_fmaf(u.x, scale, shift);
+      mu_m[j] = a.scale_events ? m.x : __builtin_fmaf(m.x, scale, shift);
+      c_u[j] = j < first ? NI : u.y;
+      h_u[j] = u.z;
+      c_m[j] = j < first ? NI : m.y;
+      h_m[j] = m.z;
+    }
+    /* columns of the previous event, su[j+1] k-mer j's: before the first event all
+     * -inf but the origin, the diagonal neighbour of the first k-mer */
+    float su[K + 1], sm[K + 1];
+#pragma unroll
+    for (int j = 0; j <= K; ++j) su[j] = sm[j] = j == first ? 0.0f : NI;
+    /* the next AHEAD events' means are loaded while these ones' rows are computed */
+    for (int32_t e = e0; e <= e1; e += AHEAD) {
+      float xs[AHEAD];
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) xs[u] = xn[u];
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) xn[u] = xm[(uint64_t)a.ev_stride * (uint64_t)min(e + AHEAD + u, e1)];
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) {
+        if (e + u > e1) break;
+        float x = xs[u];
+        if (a.scale_events) {
+          const float d = x - shift;
+          x = d / scale;
+        }
+        float du = su[0], dm = sm[0];
+        float lu = NI, lm = NI; /* left neighbours in this event's row */
+        su[0] = sm[0] = NI;
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
           const float d_u = x - mu_u[j];
           const float em_u = c_u[j] - ((d_u * d_u) * h_u[j]);
           const float d_m = x - mu_m[j];
           const float em_m = c_m[j] - ((d_m * d_m) * h_m[j]);
-          const float nu = fmaxf(fmaxf((du + rd.lp_step) + em_u, (su[j] + rd.lp_stay) + em_u), lu + rd.lp_skip);
-          const float nm = fmaxf(fmaxf((dm + rd.lp_step) + em_m, (sm[j] + rd.lp_stay) + em_m), lm + rd.lp_skip);
-          du = su[j];
-          dm = sm[j];
-          su[j] = nu;
-          sm[j] = nm;
+          const float nu = fmaxf(fmaxf((du + rd.lp_step) + em_u, (su[j + 1] + rd.lp_stay) + em_u), lu + rd.lp_skip);
+          const float nm = fmaxf(fmaxf((dm + rd.lp_step) + em_m, (sm[j + 1] + rd.lp_stay) + em_m), lm + rd.lp_skip);
+          du = su[j + 1];
+          dm = sm[j + 1];
+          su[j + 1] = nu;
+          sm[j + 1] = nm;
           lu = nu;
           lm = nm;
         }
       }
     }
-    float vu = NI, vm = NI;
-#pragma unroll
-    for (int j = 0; j < KMAX; ++j)
-      if (j == nk - 1) {
-        vu = su[j];
-        vm = sm[j];
-      }
-    a.llr[rd.km_off + i] = vm - vu;
+    a.llr[rd.km_off + i] = sm[K] - su[K];
     if (a.n_ev) a.n_ev[rd.km_off + i] = e1 - e0 + 1;
   }
 }
@@ -238,8 +312,13 @@ hipError_t launch_meth(const MethArgs &a, hipStream_t st, hipEvent_t *tev) {
       (void)hipEventRecord(tev[0], st);
     hipExtLaunchKernelGGL(k_meth_sites, dim3(a.n_kmer_tiles), dim3(256), 0, st, nullptr, tev ? tev[1] : nullptr, 0,
                           a);
-    hipExtLaunchKernelGGL(k_meth_llr, dim3(2048), dim3(256), 0, st, tev ? tev[2] : nullptr,
-                          tev ? tev[3] : nullptr, 0, a);
+    hipEvent_t t0 = tev ? tev[2] : nullptr, t1 = tev ? tev[3] : nullptr;
+    switch (a.k) {
+      case 5: hipExtLaunchKernelGGL(k_meth_llr<5>, dim3(256), dim3(LLR_LDS_THREADS), 0, st, t0, t1, 0, a); break;
+      case 6: hipExtLaunchKernelGGL(k_meth_llr<6>, dim3(256), dim3(LLR_LDS_THREADS), 0, st, t0, t1, 0, a); break;
+      case 9: hipExtLaunchKernelGGL(k_meth_llr<9>, dim3(2048), dim3(256), 0, st, t0, t1, 0, a); break;
+      default: hipExtLaunchKernelGGL(k_meth_llr<KMAX>, dim3(2048), dim3(256), 0, st, t0, t1, 0, a); break;
+    }
   }
   return hipGetLastError();
 }
