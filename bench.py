@@ -76,9 +76,11 @@ METRIC = "ABEA GCUPS + reads/s on 1 MI355X; p50/p99 per-read latency in serving 
 # mul, mul, sub), three moves 5 adds, arg-max 2 compare/selects.
 OPS_PER_CELL = 11
 # Plain (non-packed, non-fused) FP32 VALU peak of MI355X: 256 CUs x 4 SIMDs x
-# 16 lanes x 2.4 GHz.  The cell's arithmetic cannot use FMA (its rounding
-# order is fixed) nor packed FP32, so this is its issue ceiling.
-VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
+# 32 lanes x 2.4 GHz (with several wavefronts a SIMD starts a simple FP32
+# instruction of 64 lanes every 2 cycles: 2.07 measured).  The cell's arithmetic
+# cannot use FMA (its rounding order is fixed) nor packed FP32, so this is its
+# issue ceiling.
+VALU_PEAK_TOPS = 256 * 4 * 32 * 2.4e9 / 1e12
 # MI355X's published FP32 vector peak (counts an FMA as two flops and packed
 # FP32 as two lanes).
 FP32_VECTOR_PEAK_TFLOPS = 157.3
@@ -120,7 +122,7 @@ HBM_PEAK_GBS = 8000.0
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE with the same calibration factors
 # as ALIGN_TRAFFIC_BYTES; null for a workload without a measurement of the
 # current kernels.
-DETECT_TRAFFIC_BYTES = {"raw-4000-lognormal5kb": 1.5632e9}
+DETECT_TRAFFIC_BYTES = {}
 
 # serving: (time compression, reads) per load level; x1 is real time for 512
 # channels at 400 bases/s each
@@ -130,7 +132,7 @@ SERVING_LEVELS = [(1, 300), (10, 1000), (100, 4000), (1000, 20000), (3000, 30000
 # runs (FETCH_SIZE x 1.99989, WRITE_SIZE x 1.0: the factors a 1 GiB device
 # copy needs to read its known size), by workload; a workload without a
 # measurement of the current kernel reports null.
-ALIGN_TRAFFIC_BYTES = {"uneven-20000-w100": 150.22e9, "plain-4000-lognormal5kb": 6.806e9}
+ALIGN_TRAFFIC_BYTES = {}
 
 
 def log(*a):
