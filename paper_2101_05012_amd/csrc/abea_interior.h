@@ -33,9 +33,12 @@
  *     at the end of the band before;
  *   - the slots beside the band (k-mers K-1 and K+W) are cleared by
  *     v_writelane: the quiet NaN of the inline constant -1, which v_max3 passes
- *     over as it would -inf, and which equals no candidate;
+ *     over as it would -inf, and which equals no candidate.  Every cell of the
+ *     band is finite (the caller brings no event or k-mer here that could make
+ *     another), so one of v_max3's operands always is a number;
  *   - the move: the band's first cell against its last (v_readlane, then one
- *     compare against every lane, whose bit for the last cell's lane decides).
+ *     compare against every lane, whose bit for the last cell's lane decides;
+ *     both are finite, so the alternation for two cells of -inf is not here).
  *     With other wavefronts on the SIMD the rotations for the next band and the
  *     v_readlane run at raised priority: wavefronts waiting at such an
  *     instruction pass it first and the others find partners to start beside

@@ -392,10 +392,19 @@ struct WaveLds {
  * = K or K + 1, so no other slot outside a band is ever read by a cell in one,
  * and what those slots hold (scores of k-mers outside the band, or NaN from
  * stale ring entries) never reaches the band, its end cells or the trace bits
- * of its cells. */
+ * of its cells.
+ *
+ * The interior code is for finite scores: it has no alternation for a move
+ * between two cells of -inf, and a slot that it cleared could give a NaN.  Where
+ * every event and k-mer parameter is within bounds (WILD below) every cell of a
+ * band that lies in the table is finite, so neither arises.  A read that brings
+ * another value into the rings is given up (READ_AGAIN) and filled once more with
+ * `general` set, in which no band is interior: the code for the table's edges
+ * takes any value. */
+constexpr int READ_AGAIN = -1;
 template <int CPL, int RPG, int CLEAR, bool TRIM>
 __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 *trace,
-                                         float *__restrict__ lx, float4 *__restrict__ lk, int &e_end) {
+                                         float *__restrict__ lx, float4 *__restrict__ lk, int general, int &e_end) {
   /* CLEAR: slot clearing of interior bands: 0 the window; else the two edge
    * slots, 1 + W mod CPL (the interior code is written for each) */
   constexpr bool CLEAR_EDGES = CLEAR != 0;
@@ -441,7 +450,13 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
   const bool scale_ev = a.scale_events != 0;
   const float ksc = a.scale[rd.orig];
   const float ksh = a.shift[rd.orig];
-  uint32_t bad_rank = 0; /* this lane met a rank outside the model */
+  /* what this lane met: bit 0 a rank outside the model; edge kernels, bit 1 an
+   * event or a k-mer's parameters in the rings beyond the bounds below (a NaN passes
+   * no comparison).  Within them an emission is below 2^91 and a score of fewer
+   * than 2^31 bands below 2^122 */
+  constexpr uint32_t BAD_RANK = 1, WILD = 2;
+  constexpr float MAX_LEVEL = 0x1p24f, MAX_TERM = 0x1p40f;
+  uint32_t met = 0;
   /* 1 unless this is one of the longest reads, which run at raised priority (made
    * here, or the compiler keeps it in a vector register) */
   int calm;
@@ -466,7 +481,7 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
    * entry 0 read in its place) */
   auto gather = [&](uint32_t r) -> float4 {
     const bool ok = r < n_model;
-    bad_rank |= ok ? 0u : 1u;
+    met |= ok ? 0u : BAD_RANK;
     return mdl[ok ? r : 0u];
   };
   /* the slot parameters (mu', c, h) of a gathered entry */
@@ -476,12 +491,20 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
   /* event e = 64q + lane: sub-ring e mod S (the lane's low bits), entry
    * floor(e / S) mod RX/S */
   auto put_x = [&](int q, float v) {
+    if constexpr (CLEAR_EDGES) met |= __builtin_fabsf(v) <= MAX_LEVEL ? 0u : WILD;
     float *sub = lx + (lane & (S - 1)) * XS;
     const int idx = ((q * 64 + lane) >> LS) & (RXS - 1);
     sub[idx] = v;
     if (idx < G / S) sub[RXS + idx] = v;
   };
-  auto put_k = [&](int q, float4 v) { lk[(q * 64 + lane) & (RK - 1)] = v; };
+  auto put_k = [&](int q, float4 v) {
+    if constexpr (CLEAR_EDGES)
+      met |= (__builtin_fabsf(v.x) <= MAX_LEVEL) & (__builtin_fabsf(v.y) <= MAX_TERM) &
+                     (__builtin_fabsf(v.z) <= MAX_TERM)
+                 ? 0u
+                 : WILD;
+    lk[(q * 64 + lane) & (RK - 1)] = v;
+  };
 
   /* Trim states (the trim paragraph after Alg. 5.3): a column at k-mer -1
    * whose cell (e, -1) is (e-1, -1) + lp_trim, every event before the read
@@ -605,7 +628,7 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
      * in band i. */
     const int lo = lo_c, hi = hi_c;
     if constexpr (CLEAR_EDGES) {
-      K = __builtin_amdgcn_readfirstlane(K + mv_n);
+      K = K + mv_n;
     } else {
       const uint64_t mv = (b & 1) ? sk_move_mask<true>(lo, hi, NFM) : sk_move_mask<false>(lo, hi, NFM);
       K -= __builtin_amdgcn_readfirstlane((int)(uint32_t)mv);
@@ -811,7 +834,7 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
         const int kv0 = (K & -CPL) + ((lane * CPL - (K & -CPL)) & (N - 1));
         v.ak = bk + 16u * (uint32_t)(kv0 & (RK - 1));
         v.ax = bx + 4u * (uint32_t)(((ib - 2 - (kv0 + CPL - 1)) >> LS) & (RXS - 1));
-        v.K = __builtin_amdgcn_readfirstlane(K + mv_n);
+        v.K = K + mv_n;
         if constexpr (CPL == 2)
           interior<NB, CLEAR - 1>(v, W);
         else
@@ -852,15 +875,21 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
    * word), in the read's path scratch, which the walk fills only after it has
    * read them */
   int *__restrict__ kpos = reinterpret_cast<int *>(a.scratch + rd.pr_off);
-  const bool gap_ok = N - W >= CPL; /* interior bands clear CPL slots outside the band */
+  /* interior bands clear CPL slots outside the band */
+  const bool gap_ok = (N - W >= CPL) & (!CLEAR_EDGES | !general);
   while (i + G - 1 <= last) {
     K = __builtin_amdgcn_readfirstlane(K);
     E = i - 3 - K; /* band i - 1 is the latest */
+    if constexpr (CLEAR_EDGES) {
+      if (!general && ballot((met & WILD) != 0u)) return READ_AGAIN;
+    }
     /* with trim the last k-mer stays out of interior bands, whose cells the
      * end recurrence does not read.  A group moves K and E up by G together, so
-     * the next n groups are interior whatever their moves */
+     * the next n groups are interior whatever their moves (64 at most: a wild
+     * value ends the fill between two runs of them) */
     int n = 0;
     if (gap_ok & (K >= 0) & (E >= W - 1)) n = min(n_e - 1 - E, n_k - 1 - (int)trim - (K + W - 1)) / G;
+    n = min(n, 64);
     if (n > 0) {
       cells += (uint64_t)W * (uint64_t)(G * n);
       do {
@@ -896,6 +925,9 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
     const int sh = (G - gb) * CPL;
     trace[g * 64 + lane] = make_uint2(TD << sh, TU << sh);
   }
+  if constexpr (CLEAR_EDGES) {
+    if (!general && ballot((met & WILD) != 0u)) return READ_AGAIN;
+  }
 
   /* terminal cell (n_e-1, n_k-1) is in the last band if its k-mer is; with
    * trim the end cell the end recurrence chose */
@@ -912,7 +944,7 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
   }
   /* every rank of the read has passed through the k-mer ring: one outside
    * the model makes the read's outcome a bad rank, with no alignment */
-  if (ballot(bad_rank != 0u)) {
+  if (ballot((met & BAD_RANK) != 0u)) {
     if (lane == 0) {
       a.out_ll[rd.orig] = ABEA_NINF;
       if (a.out_cells) a.out_cells[rd.orig] = 0;
@@ -947,8 +979,13 @@ __global__ __launch_bounds__(64) void k_band(const AlignArgs a) {
   /* the longest reads set the kernel's duration: let them issue first */
   const bool urgent = rd.n_e + rd.n_k >= a.urgent_len;
   if (urgent) __builtin_amdgcn_s_setprio(2);
-  int e_end;
-  const int st = band_read<CPL, RPG, EDGE, TRIM>(kernel_args(), rd, a.trace + rd.tr_off, lds.band.lx, lds.band.lk, e_end);
+  int st, e_end;
+  for (int general = 0;; general = 1) {
+    KernArgs &a1 = kernel_args();
+    const ReadDesc r1 = read_desc(a1.reads, s);
+    st = band_read<CPL, RPG, EDGE, TRIM>(a1, r1, a1.trace + r1.tr_off, lds.band.lx, lds.band.lk, general, e_end);
+    if (__builtin_amdgcn_readfirstlane(st) != READ_AGAIN) break;
+  }
   if (urgent) __builtin_amdgcn_s_setprio(0);
   if (threadIdx.x == 0) {
     a.rstat[s] = st;
@@ -1168,7 +1205,7 @@ __global__ __launch_bounds__(64 * WPG, waves_per_simd(CPL, TRIM)) void k_align(c
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int w = blockIdx.x * WPG + wv;
   if (w >= a.n_workers) return;
-  int s = w;
+  int s = w, general = 0;
   for (;;) {
     KernArgs &a1 = kernel_args();
     if (s >= a1.n_reads) break;
@@ -1181,9 +1218,13 @@ __global__ __launch_bounds__(64 * WPG, waves_per_simd(CPL, TRIM)) void k_align(c
       e_end = rd.n_e - 1;
       if (st == READ_OK)
         st = band_read<CPL, RPG, EDGE, TRIM>(a1, rd, a1.trace + read_desc(a1.reads, w).tr_off, lds[wv].band.lx,
-                                             lds[wv].band.lk, e_end);
+                                             lds[wv].band.lk, general, e_end);
       else
         band_skipped(a1, rd);
+    }
+    if constexpr (EDGE != 0) {
+      general = __builtin_amdgcn_readfirstlane(st) == READ_AGAIN;
+      if (general) continue;
     }
     /* the walk reads back what this wavefront's lanes just stored; keep the
      * compiler from moving loads above the stores */
