@@ -306,7 +306,11 @@ constexpr float MAX_SQUARES = 2097152.0f; /* of the 16 samples around a boundary
 static_assert(TS == 64 * BPL, "a wavefront per tile");
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+/* words at any sample's address */
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+typedef uint32_t u32_a2 __attribute__((aligned(2)));
+static_assert(alignof(u32x4_a2) == alignof(int16_t) && alignof(u32_a2) == alignof(int16_t),
+              "loads of words promise no more than a sample's alignment");
 
 /* A tile's read as seen from the tile's first boundary: samples at x[lo .. hi],
  * boundaries of a window w defined in [w - first, last - w] (32 bits, cut off
@@ -332,12 +336,14 @@ __device__ __forceinline__ int sample_at(const TileView &v, int rel) {
   return v.x[min(max(rel, v.lo), v.hi)];
 }
 
-/* samples rel .. rel + 2*NW - 1 (rel even) of the read as pairs.  A read's
- * samples start at any even address: the words are read from multiples of four
- * bytes, from a sample before rel to two after the last. */
+/* samples rel .. rel + 2*NW - 1 of the read as pairs.  A read's samples start at
+ * any even address: for even rel (the lanes' own boundaries) the words are read
+ * from multiples of four bytes, for odd rel (half of the halo boundaries) from two
+ * bytes after one, in both cases from as much as a sample before rel to two
+ * after the last. */
 template <int NW>
 __device__ __forceinline__ void word_pairs(const TileView &v, int rel, uint32_t (&d)[NW]) {
-  const u32x4_a4 *p = reinterpret_cast<const u32x4_a4 *>(v.x + rel - v.odd);
+  const u32x4_a2 *p = reinterpret_cast<const u32x4_a2 *>(v.x + rel - v.odd);
 #pragma unroll
   for (int i = 0; i < NW / 4; ++i) {
     const u32x4 q = p[i];
@@ -347,7 +353,7 @@ __device__ __forceinline__ void word_pairs(const TileView &v, int rel, uint32_t 
     d[4 * i + 3] = q.w;
   }
   if (v.odd) {
-    const uint32_t e = reinterpret_cast<const uint32_t *>(p)[NW];
+    const uint32_t e = reinterpret_cast<const u32_a2 *>(p)[NW];
 #pragma unroll
     for (int i = 0; i < NW; ++i) d[i] = __builtin_amdgcn_alignbit(i + 1 < NW ? d[i + 1] : e, d[i], 16);
   }
