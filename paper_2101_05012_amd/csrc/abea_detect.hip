@@ -881,6 +881,11 @@ __global__ __launch_bounds__(64 * WAVES) void k_ed_events(DetectArgs a) {
   const int xt = TS + lane < left ? sample_at(tv, TS + lane) : 0;
   const uint64_t gbase = a.base[g] + a.block_sum[g / SCAN_TILES];
 
+  /* no event starts in the tile: what runs through it is summed where it starts
+   * (without this, tiles inside an event each summed the rest of it) */
+  if (i0 == 0 && lane == 0) bits |= 1u; /* a read's first event starts at sample 0 */
+  if (__ballot(bits != 0) == 0) return;
+
   /* the event that runs past the tile ends at the read's next change point: the
    * first change point of the first later tile that has one, or the read's end */
   int64_t end = left;
@@ -905,7 +910,19 @@ __global__ __launch_bounds__(64 * WAVES) void k_ed_events(DetectArgs a) {
     tq = last_lane(wave_scan((long long)(v * v)));
   } else {
     long long s = xt, q = xt * xt;
-    for (int64_t k = TS + 64 + lane; k < end; k += 64) {
+    /* eight loads in flight: one wavefront is alone with a long event */
+    int64_t k = TS + 64 + lane;
+    for (; k + 7 * 64 < end; k += 8 * 64) {
+      int v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = tv.x[k + 64 * u];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        s += v[u];
+        q += v[u] * v[u];
+      }
+    }
+    for (; k < end; k += 64) {
       const int v = tv.x[k];
       s += v;
       q += v * v;
@@ -926,7 +943,6 @@ __global__ __launch_bounds__(64 * WAVES) void k_ed_events(DetectArgs a) {
   }
   const int si = wave_scan(s);
   const long long qi = wave_scan(q);
-  if (i0 == 0 && lane == 0) bits |= 1u; /* a read's first event starts at sample 0 */
   const int ni = wave_scan((int)__popc(bits));
   const int n_ev = __builtin_amdgcn_readlane(ni, 63);
   uint4 *at = list + (ni - (int)__popc(bits));
