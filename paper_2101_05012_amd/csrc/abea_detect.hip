@@ -29,8 +29,8 @@
  *                  event count and first change point (k_ed_detect_any, a
  *                  workgroup per tile, for windows other than 3 and 8);
  *   k_ed_scan      exclusive scan of the tile counts, per 1024 tiles, then
- *                  over the blocks (k_ed_scan_top); with one block, also
- *                  k_ed_offsets' work;
+ *                  over the blocks (k_ed_scan_top); with one block and no
+ *                  more reads than it has tiles, also k_ed_offsets' work;
  *   k_ed_events    one wavefront per tile: the tile's event starts in order,
  *                  the end of its last event from the first change point of
  *                  the read's next tiles, and one lane per event for its
@@ -755,12 +755,21 @@ __device__ __forceinline__ uint64_t block_exclusive_scan(uint64_t v, uint64_t *s
 
 }  // namespace
 
+/* One block scans all tiles and makes the reads' offsets too, four reads a thread at
+ * most: 16 reads of 5 kb need 4 launches rather than 6, of 2 to 3 us each.  More reads
+ * than tiles are empty reads, and one block is slow at many (200000: 1146 us a call
+ * against 166 with a launch of their own). */
+__host__ __device__ inline bool one_block_offsets(uint32_t blocks, int n_reads) {
+  return blocks == 1 && n_reads <= SCAN_TILES;
+}
+
 /* first level: tiles [b*1024, (b+1)*1024), four consecutive per thread */
 __global__ __launch_bounds__(THREADS) void k_ed_scan(DetectArgs a) {
   __shared__ uint64_t sh[THREADS / 64];
   const uint64_t t0 = (uint64_t)blockIdx.x * SCAN_TILES + 4u * threadIdx.x;
   /* (the plan lies in host memory: requested early) */
-  const uint32_t tf = gridDim.x == 1 && (int)threadIdx.x <= a.n_reads ? a.tile_first[threadIdx.x] : 0;
+  const bool offsets = one_block_offsets(gridDim.x, a.n_reads);
+  const uint32_t tf = offsets && (int)threadIdx.x <= a.n_reads ? a.tile_first[threadIdx.x] : 0;
   uint32_t c[4];
   uint64_t s = 0;
   for (int q = 0; q < 4; ++q) {
@@ -773,12 +782,10 @@ __global__ __launch_bounds__(THREADS) void k_ed_scan(DetectArgs a) {
     if (t0 + q < a.n_tiles) a.base[t0 + q] = p;
     p += c[q];
   }
-  if (gridDim.x > 1) {
+  if (!offsets) {
     if (threadIdx.x == 0) a.block_sum[blockIdx.x] = total;
     return;
   }
-  /* a batch of one block: its sums are done, and the reads' offsets are made here
-   * (16 reads of 5 kb: 4 launches rather than 6, of 2 to 3 us each) */
   if (threadIdx.x == 0) {
     a.block_sum[0] = 0;
     a.block_sum[1] = total;
@@ -1031,7 +1038,7 @@ hipError_t launch_detect(const DetectArgs &a, hipStream_t st, hipEvent_t *tev) {
     (void)hipEventRecord(e0, st);
     (void)hipEventRecord(e1, st);
   }
-  if (nb != 1) hipLaunchKernelGGL(k_ed_scan_top, dim3(1), dim3(THREADS), 0, st, a, nb);
+  if (!one_block_offsets(nb, a.n_reads)) hipLaunchKernelGGL(k_ed_scan_top, dim3(1), dim3(THREADS), 0, st, a, nb);
   if (a.n_tiles > 0) {
     /* the event lists' room decides how many wavefronts a CU holds */
     const int most = (TS + a.w_short - 1) / a.w_short + (TS + a.w_long - 1) / a.w_long + 1;
@@ -1044,7 +1051,7 @@ hipError_t launch_detect(const DetectArgs &a, hipStream_t st, hipEvent_t *tev) {
     (void)hipEventRecord(e3, st);
   }
   const int nr = a.n_reads + 1;
-  if (nb != 1) hipLaunchKernelGGL(k_ed_offsets, dim3((nr + 255) / 256), dim3(256), 0, st, a, nb);
+  if (!one_block_offsets(nb, a.n_reads)) hipLaunchKernelGGL(k_ed_offsets, dim3((nr + 255) / 256), dim3(256), 0, st, a, nb);
   if (tev) {
     const hipError_t e = hipEventRecord(tev[5], st);
     if (e != hipSuccess) return e;
