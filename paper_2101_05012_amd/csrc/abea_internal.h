@@ -92,7 +92,8 @@ __host__ __device__ inline int path_segments(int ng, int &sl) {
  * shorter path, with trim states, has no more of either).  Never more than
  * one per band. */
 inline uint64_t path_words(uint64_t bands, int cpl) {
-  const uint64_t groups = (bands + bands_per_group(cpl) - 1) / bands_per_group(cpl);
+  const int lg = 5 - __builtin_ctz((unsigned)cpl); /* log2(bands_per_group) */
+  const uint64_t groups = (bands + (1u << lg) - 1) >> lg;
   const uint64_t n = groups / WALK_MIN_GROUPS;
   return groups + (n > 1 ? (n < WALK_MAX_SEGMENTS ? n : WALK_MAX_SEGMENTS) : 0);
 }
