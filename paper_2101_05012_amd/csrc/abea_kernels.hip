@@ -118,20 +118,36 @@ __device__ __forceinline__ float vmax3(float a, float b, float c) {
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
 }
-/* per lane: acc*2 + (a == b), a compare and one v_addc.  In interior bands the
- * compiler places them; elsewhere they stay together (the unrolled bands'
- * compares would pile up in scalar registers), the two wait states between
- * them included. */
-template <bool INTERIOR>
-__device__ __forceinline__ uint32_t shift_in_eq(uint32_t acc, float a, float b) {
-  if constexpr (INTERIOR) return acc + acc + (a == b ? 1u : 0u);
-  asm("v_cmp_eq_f32_e32 vcc, %1, %2\n\t"
-      "s_nop 1\n\t"
-      "v_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
-      : "+v"(acc)
-      : "v"(a), "v"(b)
+/* per lane: the two trace planes shifted left by one, bit 0 of td set where s == d,
+ * of tu where s == u: two compares and two v_addc, with the two wait states
+ * between a compare and the v_addc that reads its mask (the compiler, given the
+ * expression, makes a v_cndmask and a shift of each v_addc) */
+__device__ __forceinline__ void shift_in(uint32_t &td, uint32_t &tu, float s, float d, float u) {
+  uint64_t m;
+  asm("v_cmp_eq_f32_e64 %2, %3, %4\n\t"
+      "v_cmp_eq_f32_e32 vcc, %3, %5\n\t"
+      "s_nop 0\n\t"
+      "v_addc_co_u32_e64 %0, %2, %0, %0, %2\n\t"
+      "v_addc_co_u32_e32 %1, vcc, %1, %1, vcc"
+      : "+v"(td), "+v"(tu), "=&s"(m)
+      : "v"(s), "v"(d), "v"(u)
       : "vcc");
-  return acc;
+}
+/* the same for two slots, whose compares fill the wait states */
+__device__ __forceinline__ void shift_in(uint32_t &td, uint32_t &tu, float s0, float d0, float u0, float s1, float d1,
+                                         float u1) {
+  uint64_t m0, m1, m2;
+  asm("v_cmp_eq_f32_e64 %2, %5, %6\n\t"
+      "v_cmp_eq_f32_e64 %3, %5, %7\n\t"
+      "v_cmp_eq_f32_e64 %4, %8, %9\n\t"
+      "v_cmp_eq_f32_e32 vcc, %8, %10\n\t"
+      "v_addc_co_u32_e64 %0, %2, %0, %0, %2\n\t"
+      "v_addc_co_u32_e64 %1, %3, %1, %1, %3\n\t"
+      "v_addc_co_u32_e64 %0, %4, %0, %0, %4\n\t"
+      "v_addc_co_u32_e32 %1, vcc, %1, %1, vcc"
+      : "+v"(td), "+v"(tu), "=&s"(m0), "=&s"(m1), "=&s"(m2)
+      : "v"(s0), "v"(d0), "v"(u0), "v"(s1), "v"(d1), "v"(u1)
+      : "vcc");
 }
 __device__ __forceinline__ uint64_t ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
 /* lane `lane` of the result is `val` (uniform), the others keep `old`
@@ -217,10 +233,13 @@ __device__ __forceinline__ KernArgs &kernel_args() {
 }
 /* planned read s (the plan does not change while a kernel runs: scalar loads) */
 __device__ __forceinline__ ReadDesc read_desc(const ReadDesc *reads, int s) {
-  const __attribute__((address_space(4))) ReadDesc *p =
-      (const __attribute__((address_space(4))) ReadDesc *)(uint64_t)(reads + s);
+  typedef const __attribute__((address_space(4))) u32x4 Piece;
+  const Piece *p = (const Piece *)(uint64_t)(reads + s);
+  u32x4 v[sizeof(ReadDesc) / sizeof(u32x4)];
+#pragma unroll
+  for (int q = 0; q < (int)(sizeof(ReadDesc) / sizeof(u32x4)); ++q) v[q] = p[q];
   ReadDesc d;
-  __builtin_memcpy(&d, (const void *)p, sizeof d);
+  __builtin_memcpy(&d, v, sizeof d);
   return d;
 }
 __device__ __forceinline__ int fresh_lane() {
@@ -529,9 +548,10 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
   /* bits of the end cells of the latest band, for the next band's move:
    * band 1's are -inf, unless the trim cell is its first (W = 2, 3) */
   int lo_c = (trim && H == 1) ? __float_as_int(lp_trim) : ABEA_NINF_BITS, hi_c = ABEA_NINF_BITS;
-  /* edge kernels: the next band's move (1: a k-mer move), and its rotated
-   * neighbours, moved */
-  int mv_n = 0;
+  /* edge kernels: the next band's first k-mer, and its rotated neighbours, moved.
+   * (The position after the move is kept, not the move: where the two meet in a
+   * loop the compiler put the move into a vector register.) */
+  int K_n = -H;
   float lf_n = NI, dg_n = NI;
   float Spp[CPL], Sp[CPL], PM[CPL], PC[CPL], PH[CPL];
   int kvs[CPL]; /* kv(slot), the k-mer the slot holds */
@@ -599,6 +619,7 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
   const int last = n_e + n_k;
   uint32_t TD = 0, TU = 0;
   uint64_t cells = 0;
+  int edge_cells = 0; /* those of a group with cells outside the table */
 
   /* One band i = i0 + b: Spp = band i-2 (overwritten by band i), Sp = band
    * i-1.  INTERIOR: all W cells of band i are inside the DP table. */
@@ -628,7 +649,7 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
      * in band i. */
     const int lo = lo_c, hi = hi_c;
     if constexpr (CLEAR_EDGES) {
-      K = K + mv_n;
+      K = K_n;
     } else {
       const uint64_t mv = (b & 1) ? sk_move_mask<true>(lo, hi, NFM) : sk_move_mask<false>(lo, hi, NFM);
       K -= __builtin_amdgcn_readfirstlane((int)(uint32_t)mv);
@@ -638,11 +659,9 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
      * wlo <= kv < wlo + wlen (one unsigned compare against the SGPR wlo) */
     int wlo = K, wlen = W;
     if constexpr (!INTERIOR) {
-      const int klo = max(K, max(0, i - 1 - n_e));
-      const int khi = min(K + W - 1, min(n_k - 1, i - 2));
-      wlen = max(0, khi - klo + 1);
-      wlo = klo;
-      cells += (uint64_t)wlen;
+      wlo = max(K, max(0, i - 1 - n_e));
+      wlen = max(0, min(K + W, min(n_k, i - 1)) - wlo);
+      edge_cells += wlen;
     }
     /* slot s-1 of a register's first slot is the last register of lane l-1:
      * left (e, k-1) in band i-1 and diag (e-1, k-1) in band i-2, each with
@@ -651,6 +670,8 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
     if constexpr (!CLEAR_EDGES) add_rot2(Sp[CPL - 1], lp_skip, Spp[CPL - 1], lp_step, lf0, dg0);
     float nv[CPL]; /* band i; band i-2 is still read below */
     float sv[CPL]; /* band i before the window mask */
+    float sd[CPL], su[CPL]; /* its candidates: diagonal and up */
+    if (fresh) TD = TU = 0u;
     /* trim, in bands with cells outside the table: the first k-mer takes no
      * skip from the trim column (while the previous band may hold it), and
      * the trim cell (i-1, -1) of this band (while the band holds k-mer -1) */
@@ -671,8 +692,8 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
       const float t = d * d;
       const float u = t * PH[c];
       const float em = PC[c] - u;
-      const float sd = dst + em;
-      const float su = (up + lp_stay) + em;
+      sd[c] = dst + em;
+      su[c] = (up + lp_stay) + em;
       float sl = lsk;
       if constexpr (!INTERIOR && TRIM) {
         if (no_skip_in) sl = sel_cmp(sl, NI, ballot(kvs[c] == 0));
@@ -683,14 +704,16 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
        * candidates equal it: D won iff sd is the maximum; otherwise U won iff
        * su is; otherwise L.  The compares stay off the chain from one band
        * to the next */
-      sv[c] = vmax3(sd, su, sl);
+      sv[c] = vmax3(sd[c], su[c], sl);
       nv[c] = (uint32_t)(kvs[c] - wlo) < (uint32_t)wlen ? sv[c] : NI;
       if constexpr (!INTERIOR && TRIM) {
         if (trim_cell) nv[c] = sel_cmp(nv[c], up + lp_trim, ballot(kvs[c] == -1));
       }
       /* trace planes: the D bit, and the U bit (read only when D is clear) */
-      TD = shift_in_eq<INTERIOR>(fresh && c == 0 ? 0u : TD, sv[c], sd);
-      TU = shift_in_eq<INTERIOR>(fresh && c == 0 ? 0u : TU, sv[c], su);
+      if constexpr (CPL == 1)
+        shift_in(TD, TU, sv[c], sd[c], su[c]);
+      else if (c & 1)
+        shift_in(TD, TU, sv[c - 1], sd[c - 1], su[c - 1], sv[c], sd[c], su[c]);
     }
     /* the end cells of this band for the next band's move.  Both lie in the
      * band; inside the table they are never masked, so they are read from
@@ -703,8 +726,9 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
       if constexpr (CLEAR_EDGES) {
         float r, h;
         if constexpr (CPL == 2) {
-          r = sel(src[0], src[1], (sf & 1) ? ~0ull : 0ull);
-          h = sel(src[0], src[1], (sh & 1) ? ~0ull : 0ull);
+          const uint64_t m = (sf & 1) ? ~0ull : 0ull;
+          r = sel(src[0], src[1], m);
+          h = CLEAR == 2 ? r : sel(src[1], src[0], m); /* W odd: the same register's, else the other's */
         } else {
           r = end_cell_reg4(src, sf);
           h = end_cell_reg4(src, sh);
@@ -713,7 +737,7 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
          * the last end cell raised to -FLT_MAX (see sk_move_mask) */
         const int lo1 = __builtin_amdgcn_readlane(__float_as_int(r), sf >> LC);
         const uint64_t cm = (b & 1) ? sk_cmp_lane<false>(lo1, h, NFM) : sk_cmp_lane<true>(lo1, h, NFM);
-        mv_n = __builtin_amdgcn_readfirstlane((int)(cm >> (sh >> LC)) & 1);
+        K_n = K + __builtin_amdgcn_readfirstlane((int)(cm >> (sh >> LC)) & 1);
         add_rot2(nv[CPL - 1], lp_skip, Sp[CPL - 1], lp_step, lf_n, dg_n);
       } else if constexpr (CPL == 4) {
         lo_c = end_cell_bits4(src, sf);
@@ -743,7 +767,10 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
 
   /* A full group of G bands from band i: slot refill every RF bands; the
    * events of the next band pair are read from LDS while the current pair
-   * computes (the scheduling barrier keeps the reads ahead). */
+   * computes (the scheduling barrier keeps the reads ahead).  Unrolled, so that the
+   * instructions of a band fill the waits of the one before: a lone wavefront's band
+   * at the table's edge takes 147 ns at W = 100 and 257 at W = 200, in a loop of one
+   * pair 202 and 354. */
   auto group = [&](auto interior_tag, int i) {
     float xa[2][CPL], xn[2][CPL];
     refill(i, 0);
@@ -775,11 +802,12 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
     }
   };
 
-  /* nb bands from band i, the first of a group, a pair at a time (not unrolled:
-   * edge kernels run only bands with cells outside the table here, and their
-   * registers stay with the interior code). */
+  /* nb bands from band i, the first of a group: the last group of a read, which
+   * may be a part.  Four at a time, the events of a pair of bands read while the
+   * pair before computes. */
   auto few_bands = [&](int i, int nb) {
-    float xa[2][CPL], xn[2][CPL];
+    static_assert(RF % 4 == 0 || RF == 2, "a refill interval ends at a quad or is a group");
+    float xa[2][CPL], xc[2][CPL];
     TD = 0;
     TU = 0;
     refill(i, 0);
@@ -787,22 +815,25 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
     load_x(xa[1], 1);
 #pragma nounroll
     for (int b = 0;;) {
-      load_x(xn[0], b + 2);
-      load_x(xn[1], b + 3);
+      load_x(xc[0], 2);
+      load_x(xc[1], 3);
       band(std::false_type(), Spp, Sp, i + b, 0, xa[0], false);
       if (b + 1 == nb) break;
       band(std::false_type(), Sp, Spp, i + b + 1, 1, xa[1], false);
-      b += 2;
+      if (b + 2 == nb) break;
+      load_x(xa[0], 4);
+      load_x(xa[1], 5);
+      band(std::false_type(), Spp, Sp, i + b + 2, 0, xc[0], false);
+      if (b + 3 == nb) break;
+      band(std::false_type(), Sp, Spp, i + b + 3, 1, xc[1], false);
+      b += 4;
       if (b == nb) break;
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) xb[c] += 4 >> LS;
       if (b % RF == 0) {
-        refill(i + b, b);
-        load_x(xa[0], b);
-        load_x(xa[1], b + 1);
-      } else {
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-          for (int c = 0; c < CPL; ++c) xa[q][c] = xn[q][c];
+        refill(i + b, 0);
+        load_x(xa[0], 0);
+        load_x(xa[1], 1);
       }
     }
   };
@@ -834,13 +865,13 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
         const int kv0 = (K & -CPL) + ((lane * CPL - (K & -CPL)) & (N - 1));
         v.ak = bk + 16u * (uint32_t)(kv0 & (RK - 1));
         v.ax = bx + 4u * (uint32_t)(((ib - 2 - (kv0 + CPL - 1)) >> LS) & (RXS - 1));
-        v.K = K + mv_n;
+        v.K = K_n;
         if constexpr (CPL == 2)
           interior<NB, CLEAR - 1>(v, W);
         else
           interior<NB, CLEAR - 1, RES>(v, W);
         K = __builtin_amdgcn_readfirstlane(v.K);
-        mv_n = __builtin_amdgcn_readfirstlane(v.mv);
+        K_n = K + v.mv;
       };
 #pragma unroll
       for (int b = 0; b < G; b += NB) {
@@ -867,8 +898,8 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
     }
   };
 
-  /* Full groups of G bands (band i = 2 + t, group t / G): ring refill and
-   * interior test once per group, one trace word per lane per group. */
+  /* Groups of G bands (band i = 2 + t, group t / G): ring refill and interior
+   * test once per group, one trace word per lane per group. */
   int i = 2;
   uint64_t g = 0;
   /* K at the start of each group, for the walk (every lane stores the same
@@ -904,25 +935,23 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
     } else {
       advance_rings();
       kpos[g] = K;
-      if constexpr (CLEAR_EDGES)
-        few_bands(i, G);
-      else
-        group(std::false_type(), i);
+      group(std::false_type(), i);
       trace[g * 64 + lane] = make_uint2(TD, TU);
+      cells += (uint32_t)edge_cells;
+      edge_cells = 0;
       ++g;
       i += G;
     }
   }
-  /* the last, partial group */
   if (i <= last) {
     K = __builtin_amdgcn_readfirstlane(K);
     E = i - 3 - K;
     advance_rings();
     kpos[g] = K;
-    const int gb = last - i + 1;
-    few_bands(i, gb);
-    i = last + 1;
-    const int sh = (G - gb) * CPL;
+    const int nb = last - i + 1;
+    few_bands(i, nb);
+    cells += (uint32_t)edge_cells;
+    const int sh = (G - nb) * CPL;
     trace[g * 64 + lane] = make_uint2(TD << sh, TU << sh);
   }
   if constexpr (CLEAR_EDGES) {
