@@ -77,9 +77,10 @@ inline int cells_per_lane(int W) {
  * nothing. */
 constexpr int WALK_MAX_SEGMENTS = 64; /* lanes of the walking wavefront */
 constexpr int WALK_MIN_GROUPS = 4;
-/* bands a segment's walk starts above its segment.  64 reads of 1 kb take 367 /
- * 365 / 372 / 378 us and 100 reads of up to 1 Mb 308 / 303 / 303 / 304 ms at 96 /
- * 128 / 192 / 256: at 96 some segments walk again */
+/* bands a segment's walk starts above its segment, at least (W bands where that is
+ * more: the walk of one read of 60000 k-mers takes 365 us at W = 100, 783 at W = 250,
+ * 5640 there with 128).  At W = 100 100 reads of up to 1 Mb take 308 / 303 / 303 / 304
+ * ms at 96 / 128 / 192 / 256: at 96 some segments walk again */
 constexpr int WALK_OVERLAP = 128;
 __host__ __device__ inline int path_segments(int ng, int &sl) {
   int n = ng / WALK_MIN_GROUPS;

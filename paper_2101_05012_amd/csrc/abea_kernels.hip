@@ -53,6 +53,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <climits>
 #include <mutex>
 #include <type_traits>
 
@@ -364,13 +365,21 @@ struct Geom {
   static constexpr int XS = RX / S + G / S;
 };
 
-/* 16-byte pieces of a trace group (two lanes' words) that the walk keeps per
- * segment: the walk enters a group at a k-mer no higher than where it entered
- * the group above, when the pieces were requested, and falls 2-3 k-mers per 8
- * bands; a step outside them reads memory. */
+/* The walk.
+ *   NP      16-byte pieces of a trace group (two lanes' words) kept per segment: the
+ *           walk enters a group at a k-mer no higher than where it entered the
+ *           group above, when the pieces were requested, and falls 2-3 k-mers per 8
+ *           bands; a step outside them reads memory
+ *   AHEAD   groups requested ahead when one segment is walked at a time
+ *   SERIAL  trace groups up to which a path is walked in that way from the start:
+ *           1024 bands, where 64 reads of 840 bands take 31 us at W = 100 for 40 in
+ *           segments, and 6000 of 1680 bands 189 us for 94; at eight slots and more,
+ *           with two or four bands a group, 2048 (6000 of 1680: 453 us for 604) */
 template <int CPL>
 struct WalkGeom {
   static constexpr int NP = CPL == 1 ? 8 : CPL == 2 ? 6 : CPL == 4 ? 3 : 2;
+  static constexpr int AHEAD = 8;
+  static constexpr int SERIAL = (CPL <= 4 ? 1024 : 2048) * CPL / 32;
 };
 
 /* LDS of one wavefront: the band fill's event ring (S sub-rings, each with a
@@ -1037,6 +1046,80 @@ __device__ __forceinline__ uint32_t lane_scan(uint32_t v) {
   return v;
 }
 
+/* The path's steps in one trace group, cell (t, k) first, its words in T (a lane's in
+ * each lane): t and k on leaving it, and the path bits V and M of backtrack_read.
+ * Each step is a run of up moves that ends with k's fall, on the scalar unit: the
+ * words of k's lane, the run's length by one find-first-bit, 22 instructions and one
+ * branch.  With TRIM the path may end here, at k = -1. */
+template <int CPL, bool TRIM>
+__device__ __forceinline__ void walk_group(uint2 T, int lower, int &t, int &k, uint32_t &V, uint32_t &M) {
+  constexpr int LC = Log2<CPL>::v;
+  uint32_t wd, wk, m, c;
+  int b = t - lower + 1, pos, f; /* cells of the group's bands from t down */
+  /* a run of n cells that ends at bit x of V.  s_bfm makes n bits, but none for 32 */
+#define ABEA_WALK_RUN0(N, X) \
+  "s_sub_u32 %[c], 32, " N "\n\ts_lshr_b32 %[c], -1, %[c]\n\ts_lshl_b32 %[c], %[c], " X "\n\t"
+#define ABEA_WALK_RUN(N, X) "s_bfm_b32 %[c], " N ", " X "\n\t"
+#define ABEA_WALK_POS0 "s_sub_u32 %[pos], 32, %[b]\n\t"
+#define ABEA_WALK_POS(LC, CPL)                                                            \
+  "s_and_b32 %[c], %[k], " #CPL "-1\n\ts_lshl" #LC "_add_u32 %[pos], %[b], %[c]\n\t"       \
+  "s_sub_u32 %[pos], 31+" #CPL ", %[pos]\n\t"
+#define ABEA_WALK(POS, RUN, LC, COL, END)                                                                 \
+  asm(".Lstep_%=:\n\t"                                                                                     \
+      "s_lshr_b32 %[c], %[k], " #LC "\n\t"                                                                 \
+      "v_readlane_b32 %[wd], %[tx], %[c]\n\t"                                                              \
+      "v_readlane_b32 %[wk], %[ty], %[c]\n\t" POS                                                          \
+      "s_orn2_b32 %[wk], %[wd], %[wk]\n\t"                                                                 \
+      "s_lshr_b32 %[m], %[wk], %[pos]\n\t"                                                                 \
+      "s_and_b32 %[m], %[m], " #COL "\n\t"                                                                 \
+      "s_cbranch_scc0 .Lup_%=\n\t"                                                                         \
+      "s_ff1_i32_b32 %[f], %[m]\n\t"                                                                       \
+      "s_add_u32 %[pos], %[pos], %[f]\n\t"                                                                 \
+      "s_lshr_b32 %[f], %[f], " #LC "\n\t" /* the up moves */                                              \
+      "s_add_u32 %[f], %[f], 1\n\t"                                                                        \
+      "s_sub_u32 %[b], %[b], %[f]\n\t" RUN("%[f]", "%[b]")                                                 \
+      "s_or_b32 %[V], %[V], %[c]\n\t"                                                                      \
+      "s_bitset1_b32 %[M], %[b]\n\t"                                                                       \
+      "s_sub_u32 %[k], %[k], 1\n\t"                                                                        \
+      "s_bitcmp1_b32 %[wd], %[pos]\n\t"                                                                    \
+      "s_subb_u32 %[b], %[b], 0\n\t" END                                                                   \
+      "s_cmp_gt_i32 %[b], 0\n\t"                                                                           \
+      "s_cbranch_scc1 .Lstep_%=\n\t"                                                                       \
+      "s_branch .Lout_%=\n"                                                                                \
+      ".Lup_%=:\n\t" /* up to the group's end */                                                           \
+      "s_mov_b32 %[f], 0\n\t" RUN("%[b]", "%[f]")                                                          \
+      "s_or_b32 %[V], %[V], %[c]\n\t"                                                                      \
+      "s_mov_b32 %[b], 0\n"                                                                                \
+      ".Lout_%=:\n"                                                                                        \
+      : [k] "+&s"(k), [V] "+&s"(V), [M] "+&s"(M), [wd] "=&s"(wd), [wk] "=&s"(wk), [m] "=&s"(m), [c] "=&s"(c), \
+        [b] "+&s"(b), [pos] "=&s"(pos), [f] "=&s"(f)                                                        \
+      : [tx] "v"(T.x), [ty] "v"(T.y)                                                                        \
+      : "scc")
+#define ABEA_WALK_TRIM(POS, RUN, LC, COL)                                                                       \
+  if constexpr (TRIM)                                                                                      \
+    ABEA_WALK(POS, RUN, LC, COL, "s_cmp_lt_i32 %[k], 0\n\ts_cbranch_scc1 .Lout_%=\n\t");                       \
+  else                                                                                                     \
+    ABEA_WALK(POS, RUN, LC, COL, "")
+  if constexpr (LC == 0) {
+    ABEA_WALK_TRIM(ABEA_WALK_POS0, ABEA_WALK_RUN0, 0, 0xffffffff);
+  } else if constexpr (LC == 1) {
+    ABEA_WALK_TRIM(ABEA_WALK_POS(1, 2), ABEA_WALK_RUN, 1, 0x55555555);
+  } else if constexpr (LC == 2) {
+    ABEA_WALK_TRIM(ABEA_WALK_POS(2, 4), ABEA_WALK_RUN, 2, 0x11111111);
+  } else if constexpr (LC == 3) {
+    ABEA_WALK_TRIM(ABEA_WALK_POS(3, 8), ABEA_WALK_RUN, 3, 0x01010101);
+  } else {
+    ABEA_WALK_TRIM(ABEA_WALK_POS(4, 16), ABEA_WALK_RUN, 4, 0x00010001);
+  }
+  t = lower - 1 + b;
+#undef ABEA_WALK_RUN0
+#undef ABEA_WALK_RUN
+#undef ABEA_WALK_POS0
+#undef ABEA_WALK_POS
+#undef ABEA_WALK
+#undef ABEA_WALK_TRIM
+}
+
 /* Backtrack of one read (Alg. 5.1, after the band loop) by the calling
  * wavefront, from its trace tiles: writes the path as bits (path scratch), its
  * length, the trace groups it covers and the read's final status (and -inf as
@@ -1046,24 +1129,33 @@ __device__ __forceinline__ uint32_t lane_scan(uint32_t v) {
  * pairs).
  *
  * What bounds it: a step needs the trace word of its cell, and the next cell
- * depends on it, so one walk is a chain of load, decode, move (60 ns a cell
- * as a wave-uniform scalar walk, a quarter of a long read's time).  Here the
- * trace groups are cut into up to 64 segments, one lane each, walked at once.
- * Where a segment's walk starts is known only when the segment above is done,
- * so each lane starts WALK_OVERLAP bands higher, from the middle of the band
- * there (the K the band fill noted): the best paths to the cells of a band come
- * from one cell a few dozen bands below, so by the segment's top the guess has
- * met the path.  That is checked, not assumed: a lane whose walk entered its
- * segment elsewhere than the segment above left it walks again from there,
- * until every lane agrees with the one above, the topmost being exact from the
- * start.  The path is then the one cell-by-cell walk's, whatever the guesses.
+ * depends on it, so one walk is a chain of load, decode, move (60 ns a cell on the
+ * scalar unit, a quarter of a long read's time).  Here the trace groups are cut into
+ * up to 64 segments, one lane each, walked at once.  Where a segment's walk starts is
+ * known only when the segment above is done, so each lane starts W bands higher
+ * (WALK_OVERLAP at least), from the middle of the band there (the K the band fill
+ * noted): the best paths to the cells of a band come from one cell a few dozen bands
+ * below, so by the segment's top the guess has met the path.  That is checked, not
+ * assumed: a segment is wrong whose walk entered it elsewhere than the segment above
+ * left its own, the topmost being exact from the start.  The wrong ones are walked
+ * again, all at once, while that helps: a lane that was right but for the one above it
+ * is put right by it.  Where paths do not meet at all (events that fit every k-mer,
+ * or none) it does not help, and what is wrong is walked one segment after the other
+ * by the whole wavefront (walk_group), which also takes short paths from the start.
+ * The path is then the one cell-by-cell walk's, whatever the guesses.
  *
- * All lanes take a group at a time.  A step handles a run of up moves at once:
+ * At once: all lanes take a group at a time.  A step handles a run of up moves:
  * the run ends at the first cell of the column whose move lowers k (D bit, or
  * no U bit: wk = D | ~U), found by one find-first-bit over the column's bits of
  * the word.  The words a lane needs next lie in a few 16-byte pieces of the
  * group below, requested while the current group is walked (WalkGeom) and kept
- * in LDS.
+ * in LDS; a group takes 0.9 us.  One segment at a time: the same steps, 50 ns each,
+ * the groups' words requested AHEAD groups before.
+ * Measured (walk kernel): one read of 8000 k-mers 66 us at W = 100 (one cell after
+ * the other 888); 64 reads of 8000 k-mers whose events fit every k-mer 645 us (walked
+ * again segment by segment at once 1286), of random events 560; 20000 reads of 112
+ * bands 54 us (in segments 82); one of 60000 k-mers at W = 250 783 us (with
+ * WALK_OVERLAP for every W 5640).
  *
  * Path scratch of a read: one word pair (V, M) per group, bit b for the cell of
  * band g*G + b: V set if the path visits the band, M if k falls on leaving that
@@ -1076,8 +1168,8 @@ __device__ __forceinline__ void backtrack_read(KernArgs &a, const ReadDesc &rd, 
   constexpr int LC = Log2<CPL>::v;
   constexpr int LG = 5 - LC;           /* log2(G) */
   constexpr int G = 1 << LG;           /* bands per trace group */
-  constexpr int NP = WalkGeom<CPL>::NP;
-  constexpr int OV = WALK_OVERLAP / G; /* groups a lane starts above its segment */
+  typedef WalkGeom<CPL> WG;
+  constexpr int NP = WG::NP;
   constexpr uint32_t COL = CPL == 1 ? 0xffffffffu : CPL == 2 ? 0x55555555u : CPL == 4 ? 0x11111111u
                          : CPL == 8 ? 0x01010101u : 0x00010001u; /* one slot's bits of a trace word */
 
@@ -1091,6 +1183,7 @@ __device__ __forceinline__ void backtrack_read(KernArgs &a, const ReadDesc &rd, 
     }
     return;
   }
+  const int OV = max(WALK_OVERLAP, a.W) >> LG; /* groups a lane starts above its segment */
   const int n_e = rd.n_e, n_k = rd.n_k;
   const int t_start = __builtin_amdgcn_readfirstlane(e_start) + n_k - 1;
   const int gtop = t_start >> LG; /* the path's last trace group */
@@ -1117,13 +1210,16 @@ __device__ __forceinline__ void backtrack_read(KernArgs &a, const ReadDesc &rd, 
   if (lane < nseg) ++g;
   asm volatile("" ::: "memory"); /* the noted K are read before the path is written over them */
 
-  uint32_t nv = 0, nm = 0; /* path cells and M bits of the segment */
-  int t_in = 0, k_in = 0;  /* where the walk entered the segment */
-  for (;;) {
+  uint32_t nv = 0, nm = 0;     /* path cells and M bits of the segment */
+  int t_in = INT_MIN, k_in = 0; /* where the walk entered the segment */
+  uint64_t wrong = 1ull << (nseg - 1); /* the segments to be walked from where the one above left its own */
+  /* (the wrong segments are walked again at once while that leaves a quarter fewer) */
+#pragma nounroll
+  for (int before = nseg; gtop + 1 > WG::SERIAL;) {
     /* every lane from (t, k) in group g-1 down to the end of its segment.  The
      * pieces of a group around k-mer kk hold the words of lanes a0, a0-1, ...
      * with a0 odd, so that a piece's two words never straddle the ring's end;
-     * the first round only requests them */
+     * the first pass only requests them */
     int a0 = 0;
     while (ballot(g >= glo)) {
       const bool on = g >= glo;
@@ -1181,13 +1277,71 @@ __device__ __forceinline__ void backtrack_read(KernArgs &a, const ReadDesc &rd, 
      * one left its own */
     const int ta = from_above(t), ka = from_above(k);
     const bool off = lane < nseg - 1 && (t_in != ta || k_in != ka);
-    if (!ballot(off)) break;
+    wrong = ballot(off);
+    const int count = __builtin_popcountll(wrong);
+    if (count == 0 || 4 * count > 3 * before) break;
+    before = count;
     if (off) {
       g = ghi + 1;
       t = ta;
       k = ka;
       nv = nm = 0;
     }
+  }
+  /* one cell after the other: the topmost wrong segment, then those below it until
+   * the walk enters one where it was entered before; then the next wrong one */
+  while (wrong) {
+    constexpr int D = WG::AHEAD;
+    int L = 63 - __builtin_clzll(wrong);
+    int ts = t_start, ks = n_k - 1;
+    if (L < nseg - 1) {
+      ts = (int)rlane_u((uint32_t)t, L + 1);
+      ks = (int)rlane_u((uint32_t)k, L + 1);
+    }
+    int gs = min(gtop, L * sl + sl - 1), gl = L * sl;
+    uint2 T[D]; /* the words of groups gs, gs-1, .., one lane's in each lane */
+    auto row = [&](int q) { return tr[(uint64_t)max(q, 0) * 64 + lane]; };
+#pragma unroll
+    for (int d = 0; d < D; ++d) T[d] = row(gs - d);
+    uint32_t cv = 0, cm = 0;
+    bool met = false;
+    do {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        const int lower = gs << LG;
+        uint32_t V = 0, M = 0;
+        if (!(TRIM && ks < 0)) walk_group<CPL, TRIM>(T[d], lower, ts, ks, V, M);
+        pw[gs] = make_int2((int)V, (int)M);
+        cv += (uint32_t)__builtin_popcount(V);
+        cm += (uint32_t)__builtin_popcount(M);
+        T[d] = row(gs - D);
+        if (TRIM && ks < 0) { /* the path's end: nothing below */
+          for (int q = gs - 1 - lane; q >= 0; q -= 64) pw[q] = make_int2(0, 0);
+          nv = lane == L ? cv : lane < L ? 0 : nv;
+          nm = lane == L ? cm : lane < L ? 0 : nm;
+          t = lane == 0 ? ts : t;
+          k = lane == 0 ? ks : k;
+          L = -1;
+          met = true;
+          break;
+        }
+        if (gs == gl) { /* the segment's end */
+          if (lane == L) {
+            t = ts;
+            k = ks;
+            nv = cv;
+            nm = cm;
+          }
+          cv = cm = 0;
+          --L;
+          gl -= sl;
+          met = L < 0 || ((int)rlane_u((uint32_t)t_in, L) == ts && (int)rlane_u((uint32_t)k_in, L) == ks);
+          if (met) break;
+        }
+        --gs;
+      }
+    } while (!met);
+    wrong &= L < 0 ? 0 : (1ull << L) - 1ull;
   }
   const int t_end = (int)rlane_u((uint32_t)t, 0), k_end = (int)rlane_u((uint32_t)k, 0);
   const bool ok = k_end == -1 && (TRIM ? t_end >= -2 : t_end == -2);
