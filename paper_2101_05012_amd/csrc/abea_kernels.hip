@@ -627,6 +627,7 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
 
   const int last = n_e + n_k;
   uint32_t TD = 0, TU = 0;
+  float even_s = 0.0f, even_d = 0.0f, even_u = 0.0f; /* one slot per lane: an even band's, whose trace bits its odd one shifts in */
   uint64_t cells = 0;
   int edge_cells = 0; /* those of a group with cells outside the table */
 
@@ -719,9 +720,15 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
         if (trim_cell) nv[c] = sel_cmp(nv[c], up + lp_trim, ballot(kvs[c] == -1));
       }
       /* trace planes: the D bit, and the U bit (read only when D is clear) */
-      if constexpr (CPL == 1)
-        shift_in(TD, TU, sv[c], sd[c], su[c]);
-      else if (c & 1)
+      if constexpr (CPL == 1) {
+        if (b & 1) {
+          shift_in(TD, TU, even_s, even_d, even_u, sv[c], sd[c], su[c]);
+        } else {
+          even_s = sv[c];
+          even_d = sd[c];
+          even_u = su[c];
+        }
+      } else if (c & 1)
         shift_in(TD, TU, sv[c - 1], sd[c - 1], su[c - 1], sv[c], sd[c], su[c]);
     }
     /* the end cells of this band for the next band's move.  Both lie in the
@@ -845,6 +852,7 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
         load_x(xa[1], 1);
       }
     }
+    if (CPL == 1 && (nb & 1)) shift_in(TD, TU, even_s, even_d, even_u);
   };
 
   /* An interior group of an edge kernel: RPG refill intervals.  In each a lane's

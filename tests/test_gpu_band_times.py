@@ -1,7 +1,7 @@
 """Time per band of a read that has a wavefront and a SIMD to itself, against that of
 an interior band at W = 100 on the same device: bands with cells outside the
 table (a read of fewer k-mers than the band is wide has no others) at two and four
-slots per lane, globally and with trim states, and interior bands at eight slots.
+slots per lane, globally and with trim states, and interior bands at one and eight slots.
 The bounds lie between what the bands' code takes and what it took with two wait
 states of their own for each trace bit and one band's instructions at a time."""
 
@@ -53,6 +53,7 @@ def test_time_per_band():
         "W=100 edge, trim": (per_band(m, 100, True, True) / unit, 3.6),
         "W=200 edge": (per_band(m, 200, True) / unit, 3.4),
         "W=200 edge, trim": (per_band(m, 200, True, True) / unit, 6.2),
+        "W=30 interior": (per_band(m, 30, False) / unit, 0.745),
         "W=300 interior": (per_band(m, 300, False) / unit, 5.35),
     }
     print(f"interior band at W=100 {unit:.1f} ns; times it:",
