@@ -493,18 +493,12 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
   const float NI = ABEA_NINF;
   const float NFM = __int_as_float((int)0xff7fffff); /* -FLT_MAX */
 
-  auto ldx = [&](int e) -> float {
-    float v = 0.0f;
-    if (e >= 0 && e < n_e) v = xm[(int64_t)xs * e];
-    return v;
-  };
-  /* a k-mer's rank (positions outside the read take rank 0: their slots are
-   * outside the table, whatever they hold never reaches a cell of it) */
-  auto ldr = [&](int k) -> uint32_t {
-    uint32_t r = 0;
-    if (k >= 0 && k < n_k) r = rk[k];
-    return r;
-  };
+  /* an event's mean and a k-mer's rank (positions outside the read take its first or
+   * last: their slots are outside the table, whatever they hold never reaches a cell
+   * of it.  Every lane loads, with no branch around it: a load that might not be there
+   * would have the compiler wait for those before and after it alike) */
+  auto ldx = [&](int e) -> float { return xm[(int64_t)xs * min(max(e, 0), n_e - 1)]; };
+  auto ldr = [&](int k) -> uint32_t { return rk[min(max(k, 0), n_k - 1)]; };
   /* its model entry, gathered (a rank outside the model is noted, and
    * entry 0 read in its place) */
   auto gather = [&](uint32_t r) -> float4 {
@@ -582,13 +576,22 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
    * after the top one waits in registers. */
   int xtop = (E + G) >> 6;
   int ktop = (K + N + G - 1) >> 6;
-  for (int q = (E - W + 1) >> 6; q <= xtop; ++q) put_x(q, ldx(q * 64 + lane));
-  for (int q = K >> 6; q <= ktop; ++q) put_k(q, kparam(gather(ldr(q * 64 + lane))));
+  /* (requested before the rings' first quarters, whose loads are waited for: with one
+   * of these still in flight where the bands begin, the compiler has every later
+   * refill wait for all loads and stores before it, 1% of a lone read) */
   float xpend = ldx((xtop + 1) * 64 + lane);
   /* the k-mer quarter after the top one: its model entries, gathered; the
    * one after that: its ranks (two loads in a chain, each a refill ahead) */
   float4 kpend = gather(ldr((ktop + 1) * 64 + lane));
   uint32_t rpend = ldr((ktop + 2) * 64 + lane);
+  int q = (E - W + 1) >> 6;
+  do {
+    put_x(q, ldx(q * 64 + lane));
+  } while (++q <= xtop);
+  q = K >> 6;
+  do {
+    put_k(q, kparam(gather(ldr(q * 64 + lane))));
+  } while (++q <= ktop);
 
   auto advance_rings = [&]() {
     if (((E + G) >> 6) > xtop) {
@@ -933,11 +936,11 @@ __device__ __forceinline__ int band_read(KernArgs &a, const ReadDesc &rd, uint2 
     }
     /* with trim the last k-mer stays out of interior bands, whose cells the
      * end recurrence does not read.  A group moves K and E up by G together, so
-     * the next n groups are interior whatever their moves (64 at most: a wild
+     * the next n groups are interior whatever their moves (256 at most: a wild
      * value ends the fill between two runs of them) */
     int n = 0;
     if (gap_ok & (K >= 0) & (E >= W - 1)) n = min(n_e - 1 - E, n_k - 1 - (int)trim - (K + W - 1)) / G;
-    n = min(n, 64);
+    n = min(n, 256);
     if (n > 0) {
       cells += (uint64_t)W * (uint64_t)(G * n);
       do {
