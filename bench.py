@@ -300,22 +300,11 @@ def bench_plain(args, wl):
     dev = 0
     torch.cuda.set_device(dev)
     P = max(1, args.inflight)
-    # edge clearing exists at 2 and 4 slots per lane; other widths take the automatic choice
-    # slot clearing: by default edges when the batches in flight together hold
-    # at least two wavefronts per SIMD (the library sees one launch at a time),
-    # else the library's own choice; edges exist at 2 and 4 slots per lane
-    band_clear = args.band_clear
-    if band_clear < 0:
-        simds = 4 * torch.cuda.get_device_properties(dev).multi_processor_count
-        per_launch = n if args.workers <= 0 else min(n, args.workers)
-        band_clear = abea.ABEA_CLEAR_EDGES if P * per_launch >= 2 * simds else abea.ABEA_CLEAR_AUTO
-    if band_clear == abea.ABEA_CLEAR_EDGES and abea.min_cells_per_lane(W) not in (2, 4):
-        band_clear = abea.ABEA_CLEAR_AUTO
     db = abea.to_device(batch, dev)  # inputs resident in HBM, shared by all slots
     slots = []
     for _ in range(P):
         al = abea.Aligner(model.level_mean, model.level_stdv, k, W=W, device=dev, timing=True,
-                          workers=args.workers, waves_per_group=args.wpg, band_clear=band_clear,
+                          workers=args.workers, waves_per_group=args.wpg,
                           scale_events=wl.get("scale_events", False), trim=wl.get("trim", False))
         slots.append((al, abea.DeviceResult.empty(db, dev), torch.cuda.Stream(dev)))
     torch.cuda.synchronize()
@@ -378,7 +367,6 @@ def bench_plain(args, wl):
         "batches_in_flight": P,
         "alignment_launch": {"workers": args.workers} if args.workers > 0 else "one wavefront per read",
         "warmup_batches": warm,
-        "band_clear": {1: "window", 2: "edges"}.get(plan.get("band_clear"), "?"),
         "per_read_scaling": "events to the model" if wl.get("scale_events") else "model to the events",
         "trim_states": bool(wl.get("trim", False)),
     })
@@ -869,9 +857,8 @@ def bench_pipeline(args, wl):
     # in flight, each alignment launch as a pool of --workers wavefronts (the
     # plain workload's form: 16 pools of 320 fill the chip's resident slots)
     if args.workers > 0:
-        clear = abea.ABEA_CLEAR_EDGES if abea.min_cells_per_lane(W) in (2, 4) else abea.ABEA_CLEAR_AUTO
         for a2 in als:
-            a2.set_launch(workers=args.workers, waves_per_group=1, band_clear=clear)
+            a2.set_launch(workers=args.workers, waves_per_group=1)
     streams = [torch.cuda.Stream(dev) for _ in range(P)]
     pbufs = [{} for _ in range(P)]
 
@@ -1134,9 +1121,7 @@ def main():
                     help="wavefronts (reads) per workgroup of the fused kernel (default: 1 for the plain "
                          "workloads, the tuned form for the persistent ones)")
     ap.add_argument("--band-clear", type=int, default=-1, choices=(-1, 0, 1, 2),
-                    help="plain workloads: slot clearing of interior bands, 0 the library's choice, 1 window, "
-                         "2 edges; -1 (default) edges when the batches in flight hold two wavefronts per SIMD, "
-                         "else the library's choice")
+                    help="accepted for older commands, without effect (abea_launch_t.band_clear selects no kernel)")
     ap.add_argument("--tune", action="store_true", help="persistent workloads: autotune the launch form")
     ap.add_argument("--cpl", type=int, default=-1,
                     help="persistent: cells per lane (0 = smallest; default: the workload's tuned form)")

@@ -414,11 +414,12 @@ int abea_get_timings(abea_ctx *ctx, float *out, int n);
  * waves_per_group: wavefronts (reads) per workgroup of the fused kernel, 1, 2
  * or 4.  cells_per_lane: band slots per lane, 0 = the smallest power of two
  * with 64*c >= W + 2, else a power of two at least that and at most 16.
- * band_clear: the slot clearing that abea_get_plan_info reports.  It selects no
- * kernel any more (results and speed are the same for each): at 2 and 4
- * cells_per_lane bands whose cells all lie inside the DP table reset only the
- * two slots beside the band (k-mers K-1 and K+W), at the others every slot
- * outside it.
+ * band_clear: accepted, checked and reported by abea_get_plan_info and
+ * abea_graph_info, and otherwise without effect: it selects no kernel any more,
+ * and results and speed are the same for each value.  Bands whose cells all lie
+ * inside the DP table reset only the two slots beside the band (k-mers K-1 and
+ * K+W) at 2 cells_per_lane, and at 4 for bandwidths up to 251; every slot outside it
+ * at 4 and a bandwidth of 252, and at the other cells_per_lane.  The value reported:
  *   ABEA_CLEAR_WINDOW, ABEA_CLEAR_EDGES : reported as given (edges needs 2 or 4
  *       cells_per_lane);
  *   ABEA_CLEAR_AUTO (0): reported as edges at 4 cells_per_lane, and at 2 when
@@ -436,7 +437,7 @@ typedef struct {
   int32_t workers;
   int32_t waves_per_group;
   int32_t cells_per_lane;
-  int32_t band_clear; /* ABEA_CLEAR_* */
+  int32_t band_clear; /* ABEA_CLEAR_*: reported, without effect */
 } abea_launch_t;
 int abea_set_launch(abea_ctx *ctx, const abea_launch_t *launch);
 
@@ -453,7 +454,7 @@ typedef struct {
   int32_t waves_per_group;
   uint64_t trace_bytes;    /* device trace memory of the batch */
   uint64_t scratch_bytes;  /* device path scratch of the batch */
-  int32_t band_clear;      /* ABEA_CLEAR_WINDOW or ABEA_CLEAR_EDGES, as resolved */
+  int32_t band_clear;      /* the launch's band_clear as abea_set_launch says; names no kernel */
   int32_t parts;           /* split kernels: parts the batch runs in under the trace budget;
                               fused kernel: 1 */
   uint64_t trace_budget;   /* the context's trace budget in bytes (0: none) */

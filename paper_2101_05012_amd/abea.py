@@ -33,9 +33,10 @@ ABEA_F_TIMING = 1
 ABEA_F_SCALE_EVENTS = 2  # events scaled to the model: (x - shift) / scale
 ABEA_F_TRIM = 4  # trim states: events at either end may stay unaligned at ln(1/100) each
 ABEA_WORKERS_SPLIT = -1
-ABEA_CLEAR_AUTO = 0  # band_clear: the library chooses
-ABEA_CLEAR_WINDOW = 1  # every slot outside the band's cells, every band
-ABEA_CLEAR_EDGES = 2  # interior bands: only the two slots beside the band
+# band_clear: checked and reported by plan_info, without effect on results or speed
+ABEA_CLEAR_AUTO = 0  # reported by the rule of abea_launch_t
+ABEA_CLEAR_WINDOW = 1
+ABEA_CLEAR_EDGES = 2  # needs 2 or 4 cells_per_lane
 ABEA_ARENA_AUTO = 0  # arena_bytes: 0.9 of the device memory free at abea_create
 ABEA_ARENA_UNBOUNDED = (1 << 64) - 1  # arena_bytes: no trace budget
 ABEA_HOST_STAGING_CHUNK = 32 << 20
@@ -402,7 +403,7 @@ class Aligner:
                    band_clear: int = ABEA_CLEAR_AUTO) -> None:
         """Launch form (abea_set_launch): workers -1 split kernels, 0 one fused
         wavefront per read, > 0 a persistent pool with a device work queue;
-        band_clear one of ABEA_CLEAR_*."""
+        band_clear one of ABEA_CLEAR_* (reported by plan_info, without effect)."""
         L = abea_launch_t(int(workers), int(waves_per_group), int(cells_per_lane), int(band_clear))
         self._check(lib().abea_set_launch(self.handle, ctypes.byref(L)), "abea_set_launch")
 

@@ -187,12 +187,12 @@ int resident_workers(abea_ctx *ctx) {
   return std::max(1, gpc * ctx->num_cus * ctx->launch.waves_per_group);
 }
 
-/* The slot clearing that the plan reports for a launch of `waves` wavefronts
- * (the rule of abea_launch_t).  It chooses no kernel: at two and four slots per
- * lane one interior code, which clears the two edge slots, is the faster in every
- * launch (a lone wavefront 90 ns per band against 109 for clearing the window,
- * W = 100), and at the others every slot outside the band is cleared. */
-bool edge_clearing(const abea_ctx *ctx, int waves) {
+/* The band_clear that the plan reports for a launch of `waves` wavefronts (the rule
+ * of abea_launch_t).  It chooses no kernel: the band width and the slots per lane do
+ * (variant in abea_kernels.hip).  At two and four slots the interior code, which
+ * clears the two slots beside the band, is the faster in every launch: a lone
+ * wavefront 89 ns per band against 109 for clearing the window, W = 100. */
+bool reports_edges(const abea_ctx *ctx, int waves) {
   if (ctx->cpl != 2 && ctx->cpl != 4) return false;
   switch (ctx->launch.band_clear) {
     case ABEA_CLEAR_WINDOW: return false;
@@ -254,7 +254,7 @@ int plan_batch(abea_ctx *ctx, Work &w, int n, const uint64_t *eo, const uint64_t
                 (unsigned long long)(words(0) * sizeof(uint2)), (unsigned long long)budget);
   int workers = n;
   const bool pool = !split && ctx->launch.workers > 0;
-  P.edge = edge_clearing(ctx, pool ? std::min(n, ctx->launch.workers) : n);
+  P.edge_report = reports_edges(ctx, pool ? std::min(n, ctx->launch.workers) : n);
   if (pool) workers = std::min(n, std::min(ctx->launch.workers, resident_workers(ctx)));
   if (!split && budget > 0) {
     uint64_t sum = 0;
@@ -755,7 +755,7 @@ int abea_get_plan_info(const abea_ctx *ctx, abea_plan_info_t *info) {
   info->workers = P.workers;
   info->cells_per_lane = P.cpl;
   info->waves_per_group = P.wpg;
-  info->band_clear = P.edge ? ABEA_CLEAR_EDGES : ABEA_CLEAR_WINDOW;
+  info->band_clear = P.edge_report ? ABEA_CLEAR_EDGES : ABEA_CLEAR_WINDOW;
   info->parts = std::max(1, (int)P.parts.size() - 1);
   info->trace_bytes = P.n_trace * sizeof(uint2);
   info->scratch_bytes = P.n_scratch * sizeof(int2);
@@ -1017,7 +1017,7 @@ int abea_graph_info(const abea_graph *g, abea_plan_info_t *info) {
   info->workers = P.workers;
   info->cells_per_lane = P.cpl;
   info->waves_per_group = P.wpg;
-  info->band_clear = P.edge ? ABEA_CLEAR_EDGES : ABEA_CLEAR_WINDOW;
+  info->band_clear = P.edge_report ? ABEA_CLEAR_EDGES : ABEA_CLEAR_WINDOW;
   info->parts = std::max(1, (int)P.parts.size() - 1);
   info->trace_bytes = P.n_trace * sizeof(uint2);
   info->scratch_bytes = P.n_scratch * sizeof(int2);

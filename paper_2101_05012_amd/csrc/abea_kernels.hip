@@ -26,16 +26,16 @@
  *              few bands from a per-wave LDS k-mer ring; each band reads its
  *              events from an LDS event ring.  The band move (Suzuki-Kasahara
  *              rule) is a wave-uniform scalar decision.  Slots outside the band
- *              are cleared to -inf each band: every one of them, or (interior
- *              bands of launches that fill the SIMDs) only the two beside the
- *              band.  Only two trace bits per slot reach HBM (two bit planes,
+ *              are cleared each band: every one of them to -inf, or (interior
+ *              bands at two and four slots per lane, abea_interior.h) only the
+ *              two beside the band.  Only two trace bits per slot reach HBM (two bit planes,
  *              32/CPL bands per 32-bit word).
  *  k_backtrack one wavefront per read walks the path, its trace cut into up to
  *              64 segments walked at once, one lane each, from guessed starts
- *              that are checked against the segment above and walked again
- *              where they differ.  The trace bits of cell (e, k) are in group
- *              (e+k)/G, lane (k mod N)/CPL.  The path is kept as two bits per
- *              band.
+ *              that are checked against the segment above; what differs is walked
+ *              again, at once or one segment after the other.  The trace bits of
+ *              cell (e, k) are in group (e+k)/G, lane (k mod N)/CPL.  The path is
+ *              kept as two bits per band.
  *  k_align     the fused form: each wavefront fills a read's bands and then
  *              walks it, one read per wavefront or a persistent pool taking
  *              reads from a device work queue.
@@ -1486,10 +1486,9 @@ __global__ __launch_bounds__(64) void k_scan(const uint64_t *__restrict__ len, i
  * path up to and with it) and e = t - k.  gridDim.y wavefronts per planned
  * read (launch_expand), each taking a run of whole segments, so that the longest
  * reads do not leave one wavefront writing megabytes at the end of the kernel.
- * A wavefront
- * takes up to 64 groups at a time (1024 bands), one per lane: the groups'
- * counts are scanned over the lanes, each lane makes its cells into LDS, and the
- * wavefront stores them coalesced.  Bound by the 8 bytes per pair written: the
+ * A wavefront takes up to 64 groups at a time (1024 bands), one per lane: the
+ * groups' counts are scanned over the lanes, each lane makes its cells into LDS, and
+ * the wavefront stores them coalesced.  Bound by the 8 bytes per pair written: the
  * 1.2 G cells of a 20000-read job (0.5 to 200 kb) in 2.9 ms (3.4 TB/s), where
  * copying pairs from a scratch took 3.9 ms. */
 constexpr int EXPAND_BANDS = 1024;
