@@ -81,8 +81,8 @@ OPS_PER_CELL = 11
 # cannot use FMA (its rounding order is fixed) nor packed FP32, so this is its
 # issue ceiling.
 VALU_PEAK_TOPS = 256 * 4 * 32 * 2.4e9 / 1e12
-# MI355X's published FP32 vector peak (counts an FMA as two flops and packed
-# FP32 as two lanes).
+# MI355X's published FP32 vector peak: the same lanes, an FMA counted as two flops
+# (packed FP32 adds nothing to it).
 FP32_VECTOR_PEAK_TFLOPS = 157.3
 
 WORKLOADS = {
