@@ -262,9 +262,9 @@ struct MethArgs {
   float *llr;                  /* [n_kmers] */
   int32_t *n_ev;               /* [n_kmers] or null */
 };
-/* tev: null, or four events: start of k_meth_bounds's dispatch and end of
- * k_meth_sites's, start and end of k_meth_llr's. */
-hipError_t launch_meth(const MethArgs &a, hipStream_t st, hipEvent_t *tev = nullptr);
+/* cus: the device's compute units.  tev: null, or four events: start of
+ * k_meth_bounds's dispatch and end of k_meth_sites's, start and end of k_meth_llr's. */
+hipError_t launch_meth(const MethArgs &a, int cus, hipStream_t st, hipEvent_t *tev = nullptr);
 /* dst[0, words) = src[0, words) (src: device-readable pinned host memory)
  * and *n_sites = 0, by a kernel on `st` */
 hipError_t launch_meth_stage(const uint64_t *src, uint64_t *dst, size_t words, uint32_t *n_sites, hipStream_t st);

@@ -189,18 +189,21 @@ __global__ __launch_bounds__(256) void k_meth_sites(MethArgs a) {
  * What bounds it: the gathers of a site (its k-mers, their entries of two models,
  * its events), each from a cache line of its own; most miss the L1, whose pending
  * lines then hold the others up (411 us for the 2 M sites of 4000 reads of 5 kb).
- * K, the longest window, is the context's k where that is 5, 6 or 9, and else
- * KMAX: registers for the k alone, and AHEAD events requested at once (375 us).
- * Up to k = 6 both models' tables (128 KB at most) lie in LDS, one workgroup of
- * LLR_LDS_THREADS per CU: 301 us.  A window cut off by the read's start is filled
- * up in front with k-mers whose emission is -inf. */
+ * K, the longest window, is the context's k: registers for it alone, and AHEAD events
+ * requested at once (375 us).  Up to k = 6 both models' tables (128 KB at most) lie in
+ * LDS, with workgroups of LLR_LDS_THREADS: 301 us.  A window cut off by the read's
+ * start is filled up in front with k-mers whose emission is -inf. */
 constexpr int AHEAD = 4;
 constexpr int LLR_LDS_THREADS = 1024;
 template <int K>
 struct LlrModels {
+  static_assert(K >= 2 && K <= KMAX, "a site's window");
   static constexpr bool LDS = K <= 6;
   static constexpr int ENTRIES = LDS ? 1 << (2 * K) : 1;
   static constexpr int THREADS = LDS ? LLR_LDS_THREADS : 256;
+  /* workgroups: as many as the device holds at once, by their threads two a CU, by
+   * the tables' 128 KB of the CU's 160 one at k = 6; without tables 2048 */
+  static int groups(int cus) { return !LDS ? 2048 : K == 6 ? cus : 2 * cus; }
 };
 static_assert(sizeof(ModelEntry) == sizeof(float4), "an entry is read as a float4");
 
@@ -218,12 +221,11 @@ __global__ __launch_bounds__(LlrModels<K>::THREADS) void k_meth_llr(MethArgs a) 
     __syncthreads();
   }
   const float NI = -INFINITY;
-  const int k = K == KMAX ? a.k : K;
   for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < n_sites; s += gridDim.x * blockDim.x) {
     const uint2 st = a.sites[s];
     const MethRead rd = a.reads[st.x];
     const int32_t i = (int32_t)st.y;
-    const int32_t j0 = i - (k - 1) > 0 ? i - (k - 1) : 0;
+    const int32_t j0 = i - (K - 1) > 0 ? i - (K - 1) : 0;
     const int first = K - (i - j0 + 1); /* the window's first k-mer among the K */
     const int32_t e0 = a.kfirst[rd.km_off + j0], e1 = a.klast[rd.km_off + i];
     const float scale = a.scale[st.x], shift = a.shift[st.x];
@@ -303,7 +305,7 @@ hipError_t launch_meth_stage(const uint64_t *src, uint64_t *dst, size_t words, u
   return hipGetLastError();
 }
 
-hipError_t launch_meth(const MethArgs &a, hipStream_t st, hipEvent_t *tev) {
+hipError_t launch_meth(const MethArgs &a, int cus, hipStream_t st, hipEvent_t *tev) {
   if (a.n_reads > 0 && a.n_kmers > 0) {
     if (a.n_pair_tiles > 0)
       hipExtLaunchKernelGGL(k_meth_bounds, dim3(a.n_pair_tiles), dim3(256), 0, st, tev ? tev[0] : nullptr, nullptr, 0,
@@ -314,10 +316,25 @@ hipError_t launch_meth(const MethArgs &a, hipStream_t st, hipEvent_t *tev) {
                           a);
     hipEvent_t t0 = tev ? tev[2] : nullptr, t1 = tev ? tev[3] : nullptr;
     switch (a.k) {
-      case 5: hipExtLaunchKernelGGL(k_meth_llr<5>, dim3(256), dim3(LLR_LDS_THREADS), 0, st, t0, t1, 0, a); break;
-      case 6: hipExtLaunchKernelGGL(k_meth_llr<6>, dim3(256), dim3(LLR_LDS_THREADS), 0, st, t0, t1, 0, a); break;
-      case 9: hipExtLaunchKernelGGL(k_meth_llr<9>, dim3(2048), dim3(256), 0, st, t0, t1, 0, a); break;
-      default: hipExtLaunchKernelGGL(k_meth_llr<KMAX>, dim3(2048), dim3(256), 0, st, t0, t1, 0, a); break;
+#define ABEA_LLR(K)                                                                                                   \
+  case K:                                                                                                             \
+    hipExtLaunchKernelGGL(k_meth_llr<K>, dim3(LlrModels<K>::groups(cus)), dim3(LlrModels<K>::THREADS), 0, st, t0, t1, \
+                          0, a);                                                                                      \
+    break;
+      case 1: /* (no site) */
+      ABEA_LLR(2)
+      ABEA_LLR(3)
+      ABEA_LLR(4)
+      ABEA_LLR(5)
+      ABEA_LLR(6)
+      ABEA_LLR(7)
+      ABEA_LLR(8)
+      ABEA_LLR(9)
+      ABEA_LLR(10)
+      ABEA_LLR(11)
+      ABEA_LLR(12)
+#undef ABEA_LLR
+      default: return hipErrorInvalidValue;
     }
   }
   return hipGetLastError();

@@ -197,7 +197,7 @@ int abea_methylation_device(abea_ctx *ctx, const abea_batch_t *b, const abea_res
   a.llr = llr;
   a.n_ev = n_events;
   M->timed = (ctx->flags & ABEA_F_TIMING) != 0;
-  HIP_TRY(ctx, launch_meth(a, st, M->timed ? M->tev : nullptr));
+  HIP_TRY(ctx, launch_meth(a, ctx->num_cus, st, M->timed ? M->tev : nullptr));
   return work_mark(ctx, M->w, st);
 }
 
