@@ -1380,10 +1380,15 @@ __global__ __launch_bounds__(64) void k_backtrack(const AlignArgs a) {
 
 /* Wavefronts per SIMD that the fused kernel's registers must leave room for
  * (the compiler would take more registers for the bands at the table's edges,
- * which are few). */
+ * which are few).  At two and four slots per lane also the most it may leave room
+ * for: where a launch brings five a SIMD (16 batches in flight in pools of 320), a
+ * sixth place lets the wavefronts settle six on some SIMDs and four on others, whose
+ * full ones end last (4000 reads a batch, W = 100: 2510 GCUPS with 78 registers and
+ * six places, 2567 with five). */
 constexpr int waves_per_simd(int cpl, bool trim) {
   return cpl == 1 ? (trim ? 4 : 5) : cpl == 2 ? 5 : cpl == 4 ? 4 : cpl == 8 ? 2 : 1;
 }
+constexpr int most_per_simd(int cpl, bool trim) { return cpl == 2 || cpl == 4 ? waves_per_simd(cpl, trim) : 8; }
 
 /* Band fill and backtrack of a read by one wavefront, with a device work
  * queue.  Worker w (wavefront w of the grid, w < n_workers) first aligns
@@ -1394,7 +1399,9 @@ constexpr int waves_per_simd(int cpl, bool trim) {
  * plain one-launch form; fewer workers bound the trace memory (admission by
  * traceback bytes) and let the longest reads of the batch overlap the rest. */
 template <int CPL, int RPG, int WPG, int EDGE, bool TRIM>
-__global__ __launch_bounds__(64 * WPG, waves_per_simd(CPL, TRIM)) void k_align(const AlignArgs a) {
+__global__ __launch_bounds__(64 * WPG)
+    __attribute__((amdgpu_waves_per_eu(waves_per_simd(CPL, TRIM), most_per_simd(CPL, TRIM)))) void k_align(
+        const AlignArgs a) {
   __shared__ WaveLds<CPL> lds[WPG];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int w = blockIdx.x * WPG + wv;
@@ -1667,7 +1674,8 @@ static int groups_per_cu_c(int wpg) {
     case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_align<CPL, RPG, 2, EDGE, TRIM>, 128, 0); break;
     case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_align<CPL, RPG, 4, EDGE, TRIM>, 256, 0); break;
   }
-  return e == hipSuccess ? n : 0;
+  /* the runtime counts the registers used, not the room most_per_simd leaves */
+  return e == hipSuccess ? std::min(n, 4 * most_per_simd(CPL, TRIM) / wpg) : 0;
 }
 
 int align_groups_per_cu(int cpl, int wpg, bool trim, int W) {
