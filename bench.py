@@ -120,9 +120,11 @@ WORKLOADS = {
 HBM_PEAK_GBS = 8000.0
 # HBM bytes of one k_ed_events launch (the slower detection kernel), from
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE with the same calibration factors
-# as ALIGN_TRAFFIC_BYTES; null for a workload without a measurement of the
-# current kernels.
-DETECT_TRAFFIC_BYTES = {}
+# as ALIGN_TRAFFIC_BYTES, by workload and kernel; null for a workload without
+# a measurement of the current kernels.
+DETECT_TRAFFIC_BYTES = {
+    "raw-4000-lognormal5kb": {"k_ed_detect": 0.660e9, "k_ed_events": 1.339e9},
+}
 
 # serving: (time compression, reads) per load level; x1 is real time for 512
 # channels at 400 bases/s each
@@ -132,7 +134,7 @@ SERVING_LEVELS = [(1, 300), (10, 1000), (100, 4000), (1000, 20000), (3000, 30000
 # runs (FETCH_SIZE x 1.99989, WRITE_SIZE x 1.0: the factors a 1 GiB device
 # copy needs to read its known size), by workload; a workload without a
 # measurement of the current kernel reports null.
-ALIGN_TRAFFIC_BYTES = {}
+ALIGN_TRAFFIC_BYTES = {"uneven-20000-w100": 109.45e9, "plain-4000-lognormal5kb": 4.989e9}
 
 
 def log(*a):
@@ -629,7 +631,7 @@ def detect_roofline(r, workload):
     nbytes, kms = by[name]
     gbs = nbytes / (kms / 1e3) / 1e9
     return {"bound": "hbm", "kernel": name, "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": DETECT_TRAFFIC_BYTES.get(workload),
+            "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": DETECT_TRAFFIC_BYTES.get(workload, {}).get(name),
             "algorithmic_bytes": nbytes,
             "achieved_job": round((2.0 * S + 12.0 * E) / (r["ms"] / 1e3) / 1e9, 1)}
 
